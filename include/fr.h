@@ -155,8 +155,9 @@ int fr_plan_get_int(const fr_plan *plan, int key, int *value);
  *                          epilogue), FR_STAGE_HALO (the halo form's kernel with
  *                          the epilogue).  Explicit FR_OPT_FORM = FR_FORM_POINT or
  *                          FR_FORM_HALO selects that form's epilogue;
- *                          FR_FORM_AUTO takes the fastest measured per order and
- *                          precision; FR_OPT_FUSE_STAGE = 0 the separate kernel. */
+ *                          FR_FORM_AUTO takes the fastest measured per order,
+ *                          precision and lattice size; FR_OPT_FUSE_STAGE = 0 the
+ *                          separate kernel. */
 enum { FR_INFO_RESIDUAL_FORM = 100, FR_INFO_STAGE_PATH = 101 };
 enum { FR_STAGE_SEPARATE = 0, FR_STAGE_POINT = 1, FR_STAGE_HALO = 2 };
 

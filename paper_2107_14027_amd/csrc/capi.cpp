@@ -50,6 +50,24 @@ int rk_buffers(fr_plan *pl, RkBufs &b)
     return FR_OK;
 }
 
+// Stage k (0..3) of a classical RK4 (pseudo-)step of size h on the separate
+// path: the residual, then the stage kernel.  In double the stage states
+// replace the residuals: s2 is in stT, s3 in k, s4 in acc.
+int separate_stage(fr_plan *pl, int k, double *U, const RkBufs &b, double *st64, const double *B,
+                   const double *D, double a, double h, double *partial, hipStream_t st)
+{
+    const double w = k == 0 || k == 3 ? h / 6.0 : h / 3.0, cnext = k < 2 ? 0.5 * h : (k == 2 ? h : 0.0);
+    if (pl->precision == FR_F32) {
+        if (int r = residual(pl, b.stT, b.k, st)) return r;
+        return launch_stage32(pl, k, U, b.acc, st64, (float *)b.stT, (const float *)b.k, B, D, a, w,
+                              cnext, partial, st);
+    }
+    double *s2 = (double *)b.stT, *s3 = (double *)b.k, *s4 = b.acc;
+    double *const in[4] = {U, s2, s3, s4}, *const out[4] = {s3, s3, s4, s3};
+    if (int r = residual(pl, in[k], out[k], st)) return r;
+    return launch_stage64(pl, k, U, s2, out[k], in[k], B, D, a, w, cnext, partial, st);
+}
+
 bool stage_in_epilogue(const fr_plan *pl)
 {
     return stage_path(pl) != FR_STAGE_SEPARATE;
@@ -144,7 +162,9 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
         check_hip(hipHostMalloc((void **)&pl->norm_host, sizeof(double), hipHostMallocDefault),
                   "hipHostMalloc"))
         return FR_ENOMEM;
-    double *st64 = f64 ? (double *)b.stT : (double *)pl->dual.ptr + nB;
+    double *st64 = f64 ? nullptr : (double *)pl->dual.ptr + nB;
+    // the RK34 stage kernel's double copy of the stage state
+    double *rk34_st64 = f64 ? (double *)b.stT : st64;
     double *partial = (double *)pl->norm.ptr;
     double *sum = partial + cap;
     int nparts = stage_blocks(n);  // partial sums the first stage writes
@@ -157,10 +177,10 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
     // first stage of a pseudo-step (residual of the current iterate, with the
     // per-block partial sums of its velocity norm), the other three stages,
     // and the reduction + read-back of the norm into pinned host memory.
-    // With the stage updates in the fused kernel's epilogue the stage states
-    // alternate between the two stage buffers, and the double copy of the stage
-    // state that the BDF term needs (FP32) is updated in place.  A fixed source
-    // D runs on the separate stage kernel.
+    // With the stage updates in the fused kernel's epilogue the stage states go
+    // to the stage buffers in turn (double: three, which the last stage reads;
+    // single: two), and the double copy of the stage velocities that the BDF
+    // term needs (FP32) is updated in place.
     // RK34 with locally adaptive steps: the step field persists in the plan
     // while the initial step is unchanged
     const bool rk34 = pl->pseudo == 1;
@@ -175,9 +195,12 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
             pl->rk34_h0 = dtau;
         }
     }
-    const bool epi = stage_in_epilogue(pl) && !D && !rk34;
-    void *const bufs[2] = {b.stT, b.k};
-    const int o = f64 ? 0 : 1;
+    const bool epi = stage_in_epilogue(pl) && !rk34;
+    // stage k's input state and the state it produces
+    void *const s32[2] = {b.stT, b.k};
+    void *const in64[4] = {U, b.stT, b.k, b.acc};
+    auto stage_in = [&](int k) { return f64 ? in64[k] : s32[k % 2]; };
+    auto stage_out = [&](int k) { return k == 3 ? (f64 ? nullptr : s32[0]) : stage_in(k + 1); };
     // face traces ping-pong between two arrays: each stage's epilogue writes
     // those of the state it produces, so only the call's first stage runs the
     // trace kernel (stage 0 reads A and writes B, stages 1, 2, 3 alternate)
@@ -198,49 +221,44 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
     auto stage0 = [&](hipStream_t st) -> int {
         if (rk34) {
             if (int r = residual(pl, f64 ? (const void *)U : b.stT, b.k, st)) return r;
-            return launch_stage34(pl, 0, U, b.acc, err34, h34, st64, b.stT, b.k, B, D, a, tol, dtau,
+            return launch_stage34(pl, 0, U, b.acc, err34, h34, rk34_st64, b.stT, b.k, B, D, a, tol, dtau,
                                   partial, st);
         }
         if (epi) {
-            const StageSpec sp = with_traces(StageSpec{U, b.acc, nullptr, f64 ? nullptr : st64,
-                                                       bufs[o], B, partial, a, w[0], c[1], 1, 0},
-                                             chained ? trA : nullptr, trB);
-            return launch_residual_stage(pl, f64 ? (const void *)U : bufs[0], sp, &nparts, st);
+            StageSpec sp{U, b.acc, nullptr, f64 ? nullptr : st64, stage_out(0), B, partial, a, w[0],
+                         c[1], 1, 0};
+            sp.D = D;
+            return launch_residual_stage(pl, stage_in(0), with_traces(sp, chained ? trA : nullptr, trB),
+                                         &nparts, st);
         }
-        if (int r = residual(pl, f64 ? (const void *)U : b.stT, b.k, st)) return r;
-        return launch_stage(pl, true, true, U, b.acc, st64, b.stT, b.k, B, a, w[0], c[1], 1, 0,
-                            partial, st, D);
+        return separate_stage(pl, 0, U, b, st64, B, D, a, dtau, partial, st);
     };
     auto stages123 = [&](hipStream_t st) -> int {
         if (rk34) {
             for (int k = 1; k < 4; ++k) {
                 if (int r = residual(pl, b.stT, b.k, st)) return r;
-                if (int r = launch_stage34(pl, k, U, b.acc, err34, h34, st64,
+                if (int r = launch_stage34(pl, k, U, b.acc, err34, h34, rk34_st64,
                                            (k == 3 && f64) ? nullptr : b.stT, b.k, B, D, a, tol,
                                            dtau, nullptr, st))
                     return r;
             }
             return FR_OK;
         }
-        if (epi) {
-            for (int k = 1; k < 4; ++k) {
-                const bool last = k == 3;
-                void *in = bufs[(k - 1 + o) % 2];
-                void *out = last ? (f64 ? nullptr : bufs[0]) : bufs[(k + o) % 2];
-                const StageSpec sp = with_traces(
-                    StageSpec{U, b.acc, f64 ? (const double *)in : st64,
-                              (f64 || last) ? nullptr : st64, out, B, nullptr, a, w[k],
-                              last ? 0.0 : c[k + 1], 0, last},
-                    k % 2 ? trB : trA, k % 2 ? trA : trB);
-                if (int r = launch_residual_stage(pl, in, sp, nullptr, st)) return r;
-            }
-            return FR_OK;
-        }
         for (int k = 1; k < 4; ++k) {
-            if (int r = residual(pl, b.stT, b.k, st)) return r;
             const bool last = k == 3;
-            if (int r = launch_stage(pl, true, false, U, b.acc, st64, (last && f64) ? nullptr : b.stT,
-                                     b.k, B, a, w[k], last ? 0.0 : c[k + 1], 0, last, nullptr, st, D))
+            if (!epi) {
+                if (int r = separate_stage(pl, k, U, b, st64, B, D, a, dtau, nullptr, st)) return r;
+                continue;
+            }
+            StageSpec sp{U, b.acc, f64 ? (const double *)stage_in(k) : st64,
+                         (f64 || last) ? nullptr : st64, stage_out(k), B, nullptr, a, w[k],
+                         last ? 0.0 : c[k + 1], 0, last};
+            sp.s2 = (const double *)in64[1];
+            sp.s3 = (const double *)in64[2];
+            sp.D = D;
+            if (int r = launch_residual_stage(pl, stage_in(k),
+                                              with_traces(sp, k % 2 ? trB : trA, k % 2 ? trA : trB),
+                                              nullptr, st))
                 return r;
         }
         return FR_OK;
@@ -346,17 +364,19 @@ int fr_rk_step(fr_plan *pl, double *U, double dt, int nsteps, fr_stream_t sv)
     if (int rc = rk_buffers(pl, b)) return rc;
     const bool f64 = pl->precision == FR_F64;
     const int64_t n = (int64_t)fr_state_len(pl);
-    double *st64 = f64 ? (double *)b.stT : nullptr;
     int rc = FR_OK;
     if (!f64) rc = launch_to_precision(pl, U, b.stT, n, s);
     const double c[4] = {0.0, 0.5 * dt, 0.5 * dt, dt};
     const double w[4] = {dt / 6.0, dt / 3.0, dt / 3.0, dt / 6.0};
-    // stage updates in the fused kernel's epilogue: the stage states alternate
-    // between the two stage buffers (no residual array); the last stage leaves
-    // the working-precision copy of U in the first one, as the separate path does
+    // stage updates in the fused kernel's epilogue: the stage states go to the
+    // stage buffers in turn (no residual array; double: three, which the last
+    // stage reads; single: two); in single precision the last stage leaves the
+    // working-precision copy of U in the first one, as the separate path does
     const bool epi = stage_in_epilogue(pl);
-    void *const bufs[2] = {b.stT, b.k};
-    const int o = f64 ? 0 : 1;
+    void *const s32[2] = {b.stT, b.k};
+    void *const in64[4] = {U, b.stT, b.k, b.acc};
+    auto stage_in = [&](int k) { return f64 ? in64[k] : s32[k % 2]; };
+    auto stage_out = [&](int k) { return k == 3 ? (f64 ? nullptr : s32[0]) : stage_in(k + 1); };
     // face traces ping-pong between two arrays (stage 0 reads A, writes B;
     // stages 1, 2, 3 alternate): only the call's first stage runs the trace kernel
     // (the halo form needs none)
@@ -366,33 +386,25 @@ int fr_rk_step(fr_plan *pl, double *U, double dt, int nsteps, fr_stream_t sv)
         if (int r = stage_trace_buffers(pl, trA, trB)) return r;
     bool chained = false;
     auto step = [&](hipStream_t st) -> int {
-        if (epi) {
-            const void *in = f64 ? (const void *)U : bufs[0];
-            for (int k = 0; k < 4; ++k) {
-                const bool last = k == 3;
-                void *out = last ? (f64 ? nullptr : bufs[0]) : bufs[(k + o) % 2];
-                StageSpec sp{U, b.acc, nullptr, nullptr, out, nullptr, nullptr,
-                             0.0, w[k], last ? 0.0 : c[k + 1], k == 0, last};
-                if (epi_traces) {
-                    sp.tr_in = k == 0 ? (chained ? trA : nullptr) : (k % 2 ? trB : trA);
-                    sp.tr_out = k % 2 ? trA : trB;
-                }
-                sp.nx = pl->nx;
-                sp.ny = pl->ny;
-                sp.nz = pl->nz;
-                if (int r = launch_residual_stage(pl, in, sp, nullptr, st)) return r;
-                in = out;
-            }
-            return FR_OK;
-        }
         for (int k = 0; k < 4; ++k) {
-            const void *in = (k == 0 && f64) ? (const void *)U : b.stT;
-            if (int r = residual(pl, in, b.k, st)) return r;
             const bool last = k == 3;
-            if (int r = launch_stage(pl, false, false, U, b.acc, st64, last && f64 ? nullptr : b.stT,
-                                     b.k, nullptr, 0.0, w[k], last ? 0.0 : c[k + 1], k == 0, last,
-                                     nullptr, st))
-                return r;
+            if (!epi) {
+                if (int r = separate_stage(pl, k, U, b, nullptr, nullptr, nullptr, 0.0, dt, nullptr, st))
+                    return r;
+                continue;
+            }
+            StageSpec sp{U, b.acc, f64 ? (const double *)stage_in(k) : nullptr, nullptr, stage_out(k),
+                         nullptr, nullptr, 0.0, w[k], last ? 0.0 : c[k + 1], k == 0, last};
+            sp.s2 = (const double *)in64[1];
+            sp.s3 = (const double *)in64[2];
+            if (epi_traces) {
+                sp.tr_in = k == 0 ? (chained ? trA : nullptr) : (k % 2 ? trB : trA);
+                sp.tr_out = k % 2 ? trA : trB;
+            }
+            sp.nx = pl->nx;
+            sp.ny = pl->ny;
+            sp.nz = pl->nz;
+            if (int r = launch_residual_stage(pl, stage_in(k), sp, nullptr, st)) return r;
         }
         return FR_OK;
     };

@@ -140,6 +140,19 @@ __device__ __forceinline__ void flux_dot(const T U[NV], const T nv[3], T zeta, T
     }
 }
 
+// The last stage of a classical RK4 step in double, without an accumulator: the
+// stage states s2 = U + dt/2 k1, s3 = U + dt/2 k2, s4 = U + dt k3 hold the
+// earlier stages, so U + dt/6 (k1 + 2 k2 + 2 k3 + k4) =
+// U + ((s2 - U) + 2 (s3 - U) + (s4 - U)) / 3 + (dt/6) k4.  The differences are
+// exact or nearly so (neighbouring doubles); what is lost is a third of the
+// states' rounding, less than the three roundings of an accumulator of U's
+// size.  d23 = (s2 - U) + 2 (s3 - U), b = dt/6.
+__device__ __forceinline__ double rk4_last(double u, double d23, double s4, double b, double k4)
+{
+    const double d = d23 + (s4 - u);
+    return u + fma(b, k4, d * (1.0 / 3.0));
+}
+
 // 16-byte vector of the working precision
 typedef double d2v __attribute__((ext_vector_type(2)));
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -160,28 +173,7 @@ struct LinesLds {
     static constexpr bool VEC = (raw * sizeof(T)) % 16 == 0 && (EP * sizeof(T)) % 16 == 0;
     // the operator block, padded to 16 bytes
     static constexpr int OPS = (OpsLayout<M>::size * (int)sizeof(T) + 15) / 16 * 16 / (int)sizeof(T);
-    // LDS values of a batch of E elements: operators, state tile, and the
-    // directions' P and momentum parts that wait in LDS (three directions for
-    // xr = 0, two for xr = 1, none for xr = 2, 3)
-    static constexpr int values(int E, int xr)
-    {
-        return OPS + E * EP + (xr >= 2 ? 0 : (xr == 1 ? 8 : 12)) * E * NS;
-    }
 };
-
-// Whether the line form's tile loads are marked nontemporal.  They are not:
-// the halo form reads the neighbours' lines of the same state again, and
-// plain loads leave the state in the caches for them (measured 2-9% faster
-// at every order than nontemporal loads).
-#ifndef FR_TILE_NT
-#define FR_TILE_NT 0
-#endif
-template <typename V>
-__device__ __forceinline__ V tile_ld(const V *p)
-{
-    if constexpr (FR_TILE_NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
 
 // A batch's contiguous state block (nel elements from src) into the line
 // form's LDS tile (element pitch EP), in 16-byte vectors where the element
@@ -199,41 +191,14 @@ __device__ __forceinline__ void tile_load(const T *__restrict__ src, T *__restri
 #pragma unroll 4
         for (int k = threadIdx.x; k < nch; k += NT) {
             const int ek = k / CPE, o = k - ek * CPE;
-            reinterpret_cast<V *>(sU + ek * EP)[o] = tile_ld(sv + k);
+            reinterpret_cast<V *>(sU + ek * EP)[o] = sv[k];
         }
     } else {
         const int nv = nel * RAW;
 #pragma unroll 4
         for (int k = threadIdx.x; k < nv; k += NT) {
             const int ek = k / RAW, o = k - ek * RAW;
-            sU[ek * EP + o] = tile_ld(src + k);
-        }
-    }
-}
-
-// The reverse of tile_load: nel finished elements of the tile (pitch EP) to
-// their contiguous block at dst.
-template <int P, typename T, int NT>
-__device__ __forceinline__ void tile_store(const T *__restrict__ sU, T *__restrict__ dst, int nel)
-{
-    using LL = LinesLds<P, T>;
-    constexpr int EP = LL::EP, RAW = LL::raw;
-    if constexpr (LL::VEC) {
-        using V = typename V16<T>::type;
-        constexpr int VW = 16 / sizeof(T), CPE = RAW / VW;
-        const int nch = nel * CPE;
-        V *dv = reinterpret_cast<V *>(dst);
-#pragma unroll 4
-        for (int k = threadIdx.x; k < nch; k += NT) {
-            const int ek = k / CPE, o = k - ek * CPE;
-            __builtin_nontemporal_store(reinterpret_cast<const V *>(sU + ek * EP)[o], dv + k);
-        }
-    } else {
-        const int nv = nel * RAW;
-#pragma unroll 4
-        for (int k = threadIdx.x; k < nv; k += NT) {
-            const int ek = k / RAW, o = k - ek * RAW;
-            __builtin_nontemporal_store(sU[ek * EP + o], dst + k);
+            sU[ek * EP + o] = src[k];
         }
     }
 }

@@ -50,18 +50,19 @@ struct GraphCache {
 
 // One classical RK4 stage of dU/dtau = k* applied to a residual k as it is
 // produced (the fused kernel's epilogue), with k* = k - [v in V] (a s + B)
-// when B is set (dual time stepping, velocity only), s the state that produced
-// k in double:
-//   first stage: acc = U + b k*,  else acc += b k*;  s' = U + cnext k*
-//   last stage:  U = acc + b k*
-// s' goes to s_out (plan precision) and, when set, s_out64 (double); on the
-// last stage s_out (when set) receives (T) U.  partial (when set) receives one
-// sum of (k*_V)^2 per workgroup.  Every index is read and written by one
-// thread only, so s_in may equal s_out64; s_out must not be the residual
-// kernel's input.
+// when B is set (dual time stepping, velocity only), plus D when set, s the
+// state that produced k in double:
+//   s' = U + cnext k*, and on the last stage
+//   double: U = rk4_last(U, s2, s3, s, b, k*) from the three stage states
+//   single: acc = U + b k* on the first stage, else acc += b k*; U = acc
+// s' goes to s_out (plan precision) and, when set, its velocities to s_out64
+// (double); on the last stage s_out (when set) receives (T) U.  partial (when
+// set) receives one sum of (k*_V)^2 per workgroup.  Every index is read and
+// written by one thread only, so s_in may equal s_out64; s_out must not be the
+// residual kernel's input.
 struct StageSpec {
     double *U;
-    double *acc;
+    double *acc;          // single precision
     const double *s_in;   // state that produced k (null: U)
     double *s_out64;
     void *s_out;
@@ -69,6 +70,8 @@ struct StageSpec {
     double *partial;
     double a, b, cnext;
     int first, last;
+    const double *s2, *s3;   // double, last stage: the first two stage states
+    const double *D;         // fixed source, or null
     // face traces: tr_in non-null holds those of the input state (written by
     // the previous stage's epilogue), so the trace kernel is skipped; tr_out
     // non-null receives those of the state this stage produces (s', or U on
@@ -207,9 +210,16 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
 
 // time integration kernels (timeint.hip)
 int stage_blocks(int64_t n);
-int launch_stage(fr_plan *pl, bool bdf, bool norm, double *U, double *acc, double *st64,
-                 void *stT, const void *k, const double *B, double a, double b, double cnext,
-                 int first, int last, double *partial, hipStream_t s, const double *D = nullptr);
+// stage `stage` (0..3) of the separate path; single precision keeps the
+// accumulator in acc and the stage state in stT (velocities also in st64);
+// double precision keeps the stage states in place of the residuals (bufs of
+// RkStates)
+int launch_stage32(fr_plan *pl, int stage, double *U, double *acc, double *st64, float *stT,
+                   const float *k, const double *B, const double *D, double a, double b,
+                   double cnext, double *partial, hipStream_t s);
+int launch_stage64(fr_plan *pl, int stage, double *U, double *st, double *k, const double *sin,
+                   const double *B, const double *D, double a, double b, double cnext,
+                   double *partial, hipStream_t s);
 int launch_stage34(fr_plan *pl, int stage, double *U, double *acc, double *err, double *h,
                    double *st64, void *stT, const void *k, const double *B, const double *D,
                    double a, double atol, double h0, double *partial, hipStream_t s);

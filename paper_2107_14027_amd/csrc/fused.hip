@@ -17,6 +17,7 @@
 // and prefetch the next batch's global data into registers before computing
 // the current one, so every workgroup keeps a batch of loads in flight while
 // it works on LDS; the grid is sized to the number of co-resident workgroups.
+#include <algorithm>
 #include <mutex>
 
 #include "fr_device.h"
@@ -522,10 +523,10 @@ constexpr int stage_chunk()
 #endif
 }
 
-// Global loads and stores of the stage update: streams read or written once
-// per stage, marked nontemporal (NTS) where that measured faster: always in
-// the halo form's epilogue (2-7%), in the point form's except at p = 4 (where
-// it measured 5-16% slower).
+// Global loads and stores of the stage update, marked nontemporal (NTS) where
+// that measured faster: in the halo form's epilogue for states that the caches
+// cannot hold (STAGE_KEEP_BYTES), in the point form's except at p = 4 (where it
+// measured 5-16% slower).
 template <bool NTS, typename X>
 __device__ __forceinline__ X stg_ld(const X *p)
 {
@@ -539,38 +540,78 @@ __device__ __forceinline__ void stg_st(X *p, X v)
     else *p = v;
 }
 
+// The global operands of the RK stage update of one value: U; in single
+// precision the accumulator (acc), in double the stage states s2, s3 of the
+// last stage; the state that produced the residual (s: in double on the last
+// stage, else for a velocity value with the BDF source), the BDF constant and
+// the fixed source.
+struct StageOps {
+    double u, acc, s2, s3, s, b, d;
+};
+
+// The RK stage update of one value from its residual kv, in the double
+// arithmetic of the stand-alone stage kernels: the next stage state or, on the
+// last stage, the new U; in single precision also the new accumulator.  vel: a
+// velocity value; ss accumulates its squared pseudo-residual.
+template <typename T>
+__device__ __forceinline__ double stage_value(const StageSpec &sp, bool last, double kv, bool vel,
+                                              const StageOps &o, double &acc, double &ss)
+{
+    if (vel && sp.B) kv -= fma(sp.a, o.s, o.b);
+    if (sp.D) kv += o.d;
+    if (vel && sp.partial) ss = fma(kv, kv, ss);
+    if constexpr (sizeof(T) == 8) {
+        if (last) return rk4_last(o.u, fma(2.0, o.s3 - o.u, o.s2 - o.u), o.s, sp.b, kv);
+    } else {
+        acc = fma(sp.b, kv, sp.first ? o.u : o.acc);
+        if (last) return acc;
+    }
+    return fma(sp.cnext, kv, o.u);
+}
+
+// Whether a stage reads the accumulator (single precision) and the state that
+// produced its residual (velocity values only unless it is the last).
+template <typename T>
+__device__ __forceinline__ bool stage_reads_acc(const StageSpec &sp)
+{
+    return sizeof(T) == 4 && !sp.first;
+}
+
 // The RK stage update of one batch whose residual (working precision) is in
 // LDS: tile(t) is the t-th of the batch's cnt values in global order
-// ([element][variable][point], from element e0).  The double arithmetic of the
-// stand-alone stage kernel (the residual went through LDS, so nothing is
-// contracted into its last operation).  A thread (tid of nt) has at most J
-// values, taken in chunks of C: the global operands of a chunk are requested
-// before the first is used, so that the loads of a wave overlap, with a
-// bounded register cost.  With tr_out the produced state replaces the
-// residual in the tile; ss accumulates the squared velocity pseudo-residual.
+// ([element][variable][point], from element e0); it went through LDS, so
+// nothing is contracted into the residual's last operation.  A thread (tid of
+// nt) has at most J values, taken in chunks of C: the global operands of a
+// chunk are requested before the first is used, so that the loads of a wave
+// overlap, with a bounded register cost.  With tr_out the produced state
+// replaces the residual in the tile.
 template <int J, int C, int NS, typename T, bool NTS, typename Tile>
 __device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&tile, unsigned tid,
                                                    unsigned nt, unsigned cnt, int64_t e0, double &ss)
 {
+    constexpr bool D64 = sizeof(T) == 8;
     const int64_t g0 = e0 * NV * NS;
+    const double *sin = sp.s_in ? sp.s_in : sp.U;
 #pragma unroll 1
     for (int j0 = 0; j0 < J; j0 += C) {
-        double ou[C], oa[C], os[C], ob[C];
+        StageOps o[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const unsigned t = tid + (j0 + j) * nt;
             if (t < cnt) {
                 const int64_t gi = g0 + t;
-                if (!sp.last) ou[j] = stg_ld<NTS>(sp.U + gi);
-                if (!sp.first || sp.last) oa[j] = stg_ld<NTS>(sp.acc + gi);
-                if (sp.B) {
-                    const unsigned r = t / NS, q = t - r * NS;
-                    const unsigned el = r / NV, v = r - el * NV;
-                    if (v >= 1 && v <= 3) {
-                        os[j] = sp.s_in ? stg_ld<NTS>(sp.s_in + gi) : stg_ld<NTS>(sp.U + gi);
-                        ob[j] = stg_ld<NTS>(sp.B + ((int64_t)(e0 + el) * 3 + (v - 1)) * NS + q);
-                    }
+                const unsigned r = t / NS, q = t - r * NS;
+                const unsigned el = r / NV, v = r - el * NV;
+                const bool vel = sp.B && v >= 1 && v <= 3;
+                if (D64 || !sp.last || sp.first) o[j].u = stg_ld<NTS>(sp.U + gi);
+                if (stage_reads_acc<T>(sp)) o[j].acc = stg_ld<NTS>(sp.acc + gi);
+                if (D64 && sp.last) {
+                    o[j].s2 = stg_ld<NTS>(sp.s2 + gi);
+                    o[j].s3 = stg_ld<NTS>(sp.s3 + gi);
                 }
+                if (vel || (D64 && sp.last)) o[j].s = stg_ld<NTS>(sin + gi);
+                if (vel) o[j].b = stg_ld<NTS>(sp.B + ((int64_t)(e0 + el) * 3 + (v - 1)) * NS + q);
+                if (sp.D) o[j].d = stg_ld<NTS>(sp.D + gi);
             }
         }
 #pragma unroll
@@ -579,27 +620,133 @@ __device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&t
             if (t < cnt) {
                 const int64_t gi = g0 + t;
                 const unsigned v = (t / NS) % NV;
-                double kv = (double)tile(t);
-                if (v >= 1 && v <= 3) {
-                    if (sp.B) kv -= fma(sp.a, os[j], ob[j]);
-                    if (sp.partial) ss = fma(kv, kv, ss);
-                }
-                if (sp.last) {
-                    const double un = fma(sp.b, kv, oa[j]);
-                    stg_st<NTS>(sp.U + gi, un);
-                    if (sp.s_out) stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)un);
-                    if (sp.tr_out) tile(t) = (T)un;
-                } else {
-                    stg_st<NTS>(sp.acc + gi, fma(sp.b, kv, sp.first ? ou[j] : oa[j]));
-                    const double sn = fma(sp.cnext, kv, ou[j]);
-                    if (sp.s_out64) stg_st<NTS>(sp.s_out64 + gi, sn);
-                    stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)sn);
-                    if (sp.tr_out) tile(t) = (T)sn;
-                }
+                const bool vel = v >= 1 && v <= 3;
+                double acc;
+                const double next = stage_value<T>(sp, sp.last, (double)tile(t), vel, o[j], acc, ss);
+                if (sp.last) stg_st<NTS>(sp.U + gi, next);
+                else if (!D64) stg_st<NTS>(sp.acc + gi, acc);
+                if (vel && sp.s_out64) stg_st<NTS>(sp.s_out64 + gi, next);
+                if (sp.s_out) stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)next);
+                if (sp.tr_out) tile(t) = (T)next;
             }
         }
     }
 }
+
+// Pairs of consecutive values of an element, v0 and v0 + 1, in one 16-byte
+// access; v0 = -1 or v0 + 1 = RAW leaves one of the two.
+template <int RAW, bool NTS>
+__device__ __forceinline__ void pair_ld(const double *p, int v0, double &x0, double &x1)
+{
+    if (v0 >= 0 && v0 + 1 < RAW) {
+        const d2v x = stg_ld<NTS>(reinterpret_cast<const d2v *>(p + v0));
+        x0 = x[0];
+        x1 = x[1];
+    } else if (v0 < 0) {
+        x1 = stg_ld<NTS>(p);
+    } else if (v0 < RAW) {
+        x0 = stg_ld<NTS>(p + v0);
+    }
+}
+template <int RAW, bool NTS>
+__device__ __forceinline__ void pair_st(double *p, int v0, double x0, double x1)
+{
+    if (v0 >= 0 && v0 + 1 < RAW) {
+        const d2v x = {x0, x1};
+        stg_st<NTS>(reinterpret_cast<d2v *>(p + v0), x);
+    } else if (v0 < 0) {
+        stg_st<NTS>(p, x1);
+    } else if (v0 < RAW) {
+        stg_st<NTS>(p + v0, x0);
+    }
+}
+
+// The same for elements that need not follow each other: the residual of
+// element elem(s) (negative: slot not in use) of slot s < E starts at tile(s,
+// elem(s)).  A unit is 64 pairs of values of one element, one pair per lane
+// (16-byte accesses of the double arrays: the pairs start at the element's
+// first 16-byte boundary, so an odd element's first value, or a last one, may
+// be alone in its pair); every wave (of NW) takes C units at a time, from unit
+// u0 on in steps of NW: request() issues the loads of their operands, apply()
+// uses them.
+template <bool LAST, bool NTS, int E, int NW, int C, int NS, typename T>
+struct StageSlots {
+    static constexpr bool D64 = sizeof(T) == 8;
+    static constexpr int RAW = NV * NS, UN = (RAW / 2 + 1 + 63) / 64, STEP = C * NW;
+    StageOps o[C][2];
+
+    template <typename Elem>
+    __device__ __forceinline__ void request(const StageSpec &sp, Elem &&elem, int u0)
+    {
+        const int lane = threadIdx.x & 63;
+        const double *sin = sp.s_in ? sp.s_in : sp.U;
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const int u = u0 + j * NW, s = u / UN;
+            const int e = u < E * UN ? elem(s) : -1;
+            if (e < 0) continue;
+            const int v0 = ((u - s * UN) * 64 + lane) * 2 - ((e * RAW) & 1);
+            const int64_t g0 = (int64_t)e * RAW;
+            if (D64 || !LAST) pair_ld<RAW, NTS>(sp.U + g0, v0, o[j][0].u, o[j][1].u);
+            if (stage_reads_acc<T>(sp)) pair_ld<RAW, NTS>(sp.acc + g0, v0, o[j][0].acc, o[j][1].acc);
+            if (D64 && LAST) {
+                pair_ld<RAW, NTS>(sp.s2 + g0, v0, o[j][0].s2, o[j][1].s2);
+                pair_ld<RAW, NTS>(sp.s3 + g0, v0, o[j][0].s3, o[j][1].s3);
+                pair_ld<RAW, NTS>(sin + g0, v0, o[j][0].s, o[j][1].s);
+            }
+            if (sp.D) pair_ld<RAW, NTS>(sp.D + g0, v0, o[j][0].d, o[j][1].d);
+            if (sp.B) {
+                const double *Be = sp.B + (int64_t)e * (3 * NS) - NS;
+#pragma unroll
+                for (int w = 0; w < 2; ++w)
+                    if (v0 + w >= NS && v0 + w < 4 * NS) {
+                        if (!(D64 && LAST)) o[j][w].s = stg_ld<NTS>(sin + g0 + v0 + w);
+                        o[j][w].b = stg_ld<NTS>(Be + v0 + w);
+                    }
+            }
+        }
+    }
+
+    template <typename Elem, typename Tile>
+    __device__ __forceinline__ void apply(const StageSpec &sp, Elem &&elem, Tile &&tile, int u0, double &ss)
+    {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const int u = u0 + j * NW, s = u / UN;
+            const int e = u < E * UN ? elem(s) : -1;
+            if (e < 0) continue;
+            const int v0 = ((u - s * UN) * 64 + lane) * 2 - ((e * RAW) & 1);
+            if (v0 >= RAW) continue;
+            const int64_t g0 = (int64_t)e * RAW;
+            const T *R = tile(s, e);
+            double acc[2], next[2];
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const int v = v0 + w;
+                if (v >= 0 && v < RAW)
+                    next[w] = stage_value<T>(sp, LAST, (double)R[v], v >= NS && v < 4 * NS, o[j][w], acc[w], ss);
+            }
+            if constexpr (LAST) pair_st<RAW, NTS>(sp.U + g0, v0, next[0], next[1]);
+            else if constexpr (!D64) pair_st<RAW, NTS>(sp.acc + g0, v0, acc[0], acc[1]);
+            if (!LAST && sp.s_out64 && v0 + 1 >= NS && v0 < 4 * NS) pair_st<RAW, NTS>(sp.s_out64 + g0, v0, next[0], next[1]);
+            if (sp.s_out) {
+                T *so = static_cast<T *>(sp.s_out) + g0;
+                if constexpr (D64) {
+                    pair_st<RAW, NTS>(so, v0, next[0], next[1]);
+                } else if (v0 >= 0 && v0 + 1 < RAW) {
+                    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+                    const f2u x = {(float)next[0], (float)next[1]};
+                    stg_st<NTS>(reinterpret_cast<f2u *>(so + v0), x);
+                } else if (v0 < 0) {
+                    stg_st<NTS>(so, (T)next[1]);
+                } else {
+                    stg_st<NTS>(so + v0, (T)next[0]);
+                }
+            }
+        }
+    }
+};
 
 // The stage epilogue needs the residual of a whole batch in the state tile:
 // the line-task path leaves it there; the point-wise path holds it in
@@ -1169,22 +1316,27 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 // derivatives (three velocities, three momentum fluxes; Table 1 stages 3 and 5
 // with the operator Dt and the correction derivatives g_L', g_R').  The
 // auxiliary residuals (a, d) are complete at that point and replace S_ad in the
-// tile.  The P and momentum parts of the three directions are summed in the
-// order x, y, z; where they wait for the sum is a per-shape choice (XR):
-//   0  each direction's parts in LDS slots of their own ([3][E][4][m^3]); the
-//      final pass sums them while it writes R
-//   1  the x direction's in its lanes' registers, y and z in LDS; the x lanes
-//      sum and write P and momentum, the auxiliary residuals are copied
-//   2  all in registers; after a barrier (the state's P and velocity values are
-//      dead by then) the x lanes store theirs over those values, the y lanes
-//      add theirs, the z lanes add and scale, and the finished tile is R
-//   3  as 2, but the momentum parts are summed between the line task's two
-//      halves (after every lane has read the tile's P and velocities for the
-//      last time) and the P parts after the second, so that the flux half's
-//      and the velocity half's results are never held in registers together
-// Modes 2 and 3 need no LDS beyond the tile (more workgroups per CU), at the
-// cost of registers and more barriers; mode 3 holds about as many registers
-// as mode 0 and is the default.  All four give the same bits.
+// tile.  The P and momentum parts of the three directions are summed over the
+// tile's P and velocity values in the order x, y, z (the x lanes store, the y
+// lanes add, the z lanes add and scale): the momentum parts between the line
+// task's two halves, after every lane has read the tile's P and velocities for
+// the last time, and the P parts after the second half, so that no LDS beyond the
+// tile is needed and the flux half's and the velocity half's results are never
+// held in registers together.  The finished tile is R.
+//
+// What bounds it: with the neighbours' traces left out the p = 6, 40^3 residual in
+// double takes 0.84 ms (5.4 TB/s), with them 1.25; compute alone 0.56.  A CU holds
+// 12 waves (140-168 VGPRs in double), three of a workgroup, so loads, compute and
+// stores of different workgroups overlap, but the 42 m^3 neighbour values per
+// element still cost their way through L1 and L2.  The state goes straight to LDS
+// (no registers, one memory latency instead of one for every four loads of a
+// thread) while the neighbours' lines are read, and XCD k works on a contiguous
+// eighth of a layer (brick_of).  Before and after, whole residual, ms, on the
+// order-sweep lattices:
+//   double  p = 1..6  0.93 1.05 0.91 1.23 1.29 1.52 -> 0.85 0.94 0.84 0.98 1.04 1.25
+//   single  p = 1..6  0.55 0.62 0.44 0.66 0.70 0.84 -> 0.53 0.56 0.40 0.52 0.54 0.68
+// More waves by spilling (a waves-per-SIMD hint), workgroups of more waves (E and
+// LW doubled) and bricks ordered in pencils measured slower or equal.
 // ---------------------------------------------------------------------------
 #ifndef FR_LE1_D
 #define FR_LE1_D 16
@@ -1241,16 +1393,16 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 #define FR_LW3_F 1
 #endif
 #ifndef FR_LE4_F
-#define FR_LE4_F 5
+#define FR_LE4_F 2
 #endif
 #ifndef FR_LW4_F
-#define FR_LW4_F 2
+#define FR_LW4_F 1
 #endif
 #ifndef FR_LE5_F
-#define FR_LE5_F 3
+#define FR_LE5_F 1
 #endif
 #ifndef FR_LW5_F
-#define FR_LW5_F 2
+#define FR_LW5_F 1
 #endif
 #ifndef FR_LE6_F
 #define FR_LE6_F 1
@@ -1259,42 +1411,6 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 #define FR_LW6_F 1
 #endif
 
-#ifndef FR_LX1_D
-#define FR_LX1_D 3
-#endif
-#ifndef FR_LX2_D
-#define FR_LX2_D 3
-#endif
-#ifndef FR_LX3_D
-#define FR_LX3_D 3
-#endif
-#ifndef FR_LX4_D
-#define FR_LX4_D 3
-#endif
-#ifndef FR_LX5_D
-#define FR_LX5_D 3
-#endif
-#ifndef FR_LX6_D
-#define FR_LX6_D 3
-#endif
-#ifndef FR_LX1_F
-#define FR_LX1_F 3
-#endif
-#ifndef FR_LX2_F
-#define FR_LX2_F 3
-#endif
-#ifndef FR_LX3_F
-#define FR_LX3_F 0
-#endif
-#ifndef FR_LX4_F
-#define FR_LX4_F 3
-#endif
-#ifndef FR_LX5_F
-#define FR_LX5_F 3
-#endif
-#ifndef FR_LX6_F
-#define FR_LX6_F 3
-#endif
 // FR_FORM_AUTO's choice per order and precision (0: point form with the trace
 // kernel, 1: line form with the trace kernel, 2: halo form, no trace kernel),
 // from the measured whole-residual times on the order-sweep lattices (periodic
@@ -1357,7 +1473,7 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 #define FR_LV4_D FR_LV_DEFAULT
 #endif
 #ifndef FR_LV5_D
-#define FR_LV5_D FR_LV_DEFAULT
+#define FR_LV5_D 3
 #endif
 #ifndef FR_LV6_D
 #define FR_LV6_D 3
@@ -1380,75 +1496,63 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 #ifndef FR_LV6_F
 #define FR_LV6_F FR_LV_DEFAULT
 #endif
-// How fr_rk_step and fr_dual_step apply the RK stage update when the plan's
-// residual is the halo form by the automatic choice, per order and precision
-// (FR_STAGE_SEPARATE: the halo-form residual, then the separate stage kernel;
-// FR_STAGE_POINT: the point form's kernel with the epilogue; FR_STAGE_HALO: the
-// halo form's kernel with the epilogue), from the measured RK4 step and dual
-// pseudo-step times on Taylor-Green lattices of 1.8-33.6 M points (the dual
-// pseudo-step decides).
-#ifndef FR_SA1_D
-#define FR_SA1_D FR_STAGE_HALO
+#ifndef FR_LSV1_D
+#define FR_LSV1_D 1
 #endif
-#ifndef FR_SA2_D
-#define FR_SA2_D FR_STAGE_HALO
+#ifndef FR_LSV2_D
+#define FR_LSV2_D 1
 #endif
-#ifndef FR_SA3_D
-#define FR_SA3_D FR_STAGE_HALO
+#ifndef FR_LSV3_D
+#define FR_LSV3_D 1
 #endif
-#ifndef FR_SA4_D
-#define FR_SA4_D FR_STAGE_POINT
+#ifndef FR_LSV4_D
+#define FR_LSV4_D 1
 #endif
-#ifndef FR_SA5_D
-#define FR_SA5_D FR_STAGE_HALO
+#ifndef FR_LSV5_D
+#define FR_LSV5_D 3
 #endif
-#ifndef FR_SA6_D
-#define FR_SA6_D FR_STAGE_HALO
+#ifndef FR_LSV6_D
+#define FR_LSV6_D 3
 #endif
-#ifndef FR_SA1_F
-#define FR_SA1_F FR_STAGE_HALO
+#ifndef FR_LSV1_F
+#define FR_LSV1_F 1
 #endif
-#ifndef FR_SA2_F
-#define FR_SA2_F FR_STAGE_HALO
+#ifndef FR_LSV2_F
+#define FR_LSV2_F 1
 #endif
-#ifndef FR_SA3_F
-#define FR_SA3_F FR_STAGE_HALO
+#ifndef FR_LSV3_F
+#define FR_LSV3_F 1
 #endif
-#ifndef FR_SA4_F
-#define FR_SA4_F FR_STAGE_HALO
+#ifndef FR_LSV4_F
+#define FR_LSV4_F 1
 #endif
-#ifndef FR_SA5_F
-#define FR_SA5_F FR_STAGE_POINT
+#ifndef FR_LSV5_F
+#define FR_LSV5_F 1
 #endif
-#ifndef FR_SA6_F
-#define FR_SA6_F FR_STAGE_HALO
+#ifndef FR_LSV6_F
+#define FR_LSV6_F 1
 #endif
-template <int P, typename T> struct StageAuto;
-#define FR_SAUTO(PP, TT, S) \
-    template <> struct StageAuto<PP, TT> { static constexpr int value = FR_SA##PP##_##S; };
-FR_SAUTO(1, double, D)
-FR_SAUTO(2, double, D)
-FR_SAUTO(3, double, D)
-FR_SAUTO(4, double, D)
-FR_SAUTO(5, double, D)
-FR_SAUTO(6, double, D)
-FR_SAUTO(1, float, F)
-FR_SAUTO(2, float, F)
-FR_SAUTO(3, float, F)
-FR_SAUTO(4, float, F)
-FR_SAUTO(5, float, F)
-FR_SAUTO(6, float, F)
-#undef FR_SAUTO
+// Largest lattice (elements) on which fr_rk_step and fr_dual_step apply the RK
+// stage update in the point form's kernel when the plan's residual is the halo
+// form by the automatic choice; larger ones take the halo form's epilogue.  RK4
+// steps, point against halo form: p = 4 in double 47 and 51 us on 4^3 hexes, 83
+// and 92 on 10^3, 137 and 126 on 12^3, 11.0 and 7.0 ms on 51^3 (few workgroups
+// leave the point form's trace pass cheap); p = 5 in single precision is within
+// 5% on a dozen elements (46 and 44 us) and 168 against 107 us on 10^3.
+template <int P, typename T>
+constexpr int stage_point_most()
+{
+    constexpr int d[PMAX + 1] = {0, 0, 0, 0, 1024, 0, 0}, f[PMAX + 1] = {0, 0, 0, 0, 0, 16, 0};
+    return sizeof(T) == 8 ? d[P] : f[P];
+}
 
 template <int P, typename T> struct LinesShape;
 #define FR_LSHAPE(PP, TT, S)                                                        \
     template <> struct LinesShape<PP, TT> {                                         \
         static constexpr int E = FR_LE##PP##_##S, W = FR_LW##PP##_##S, NT = 192 * W; \
         static_assert(E * (PP + 1) * (PP + 1) <= 64 * W, "one lane per line");       \
-        static constexpr int XR = FR_LX##PP##_##S;                                   \
         static constexpr int AUTO = FR_LA##PP##_##S;                                 \
-        static constexpr int WPE = FR_LV##PP##_##S;                                  \
-        static_assert(LinesLds<PP, TT>::values(E, XR) * sizeof(TT) <= 160 * 1024, "LDS"); \
+        static constexpr int WPE = FR_LV##PP##_##S, SWPE = FR_LSV##PP##_##S;         \
     };
 FR_LSHAPE(1, double, D)
 FR_LSHAPE(2, double, D)
@@ -1543,15 +1647,6 @@ __device__ __forceinline__ void line_put(T *__restrict__ p, const T (&x)[M])
     }
 }
 
-// Whether the line task's row loop stays rolled (per order and precision;
-// fewer live registers against loop overhead).
-#ifndef FR_LROLL
-#define FR_LROLL 1
-#endif
-template <int P, typename T> struct LinesRolled {
-    static constexpr bool value = FR_LROLL != 0;
-};
-
 // One direction's line task on the element tile Ut (LDS, updated in place),
 // in three phases that a caller may separate by barriers:
 //   lt_fluxes      the line's own traces (k_trace's chain), the two common
@@ -1562,8 +1657,7 @@ template <int P, typename T> struct LinesRolled {
 //                  replace S_aD in the tile (only this lane touches those
 //                  values) and the P part zeta n_DD du_D/dxi_D + dissipation
 // sop: the operator block in LDS; oth{m,p}: the neighbours' traces on the
-// line's two face points.  The P and momentum parts go to sCd (this
-// direction's [4][m^3] slots of the element) or, with XR, to ctb[0..3][r] in
+// line's two face points.  The P and momentum parts go to ctb[0..3][r] in
 // registers.
 template <int P, typename T, int D>
 __device__ __forceinline__ int lt_base(int L)
@@ -1573,11 +1667,11 @@ __device__ __forceinline__ int lt_base(int L)
     return D == 0 ? M * L : (D == 1 ? a + M * M * b : L);
 }
 
-template <int P, typename T, int D, bool XR>
+template <int P, typename T, int D>
 __device__ __forceinline__ void lt_fluxes(T *__restrict__ Ut, const T *__restrict__ sop,
                                           const T (&othm)[NTR], const T (&othp)[NTR],
-                                          const Consts<T> &c, int L, T *__restrict__ sCd,
-                                          T (&ctb)[4][P + 1], T (&FIm)[NTR], T (&FIp)[NTR])
+                                          const Consts<T> &c, int L, T (&ctb)[4][P + 1],
+                                          T (&FIm)[NTR], T (&FIp)[NTR])
 {
     constexpr int M = P + 1, NS = M * M * M;
     constexpr int STR = D == 0 ? 1 : (D == 1 ? M : M * M);
@@ -1646,26 +1740,17 @@ __device__ __forceinline__ void lt_fluxes(T *__restrict__ Ut, const T *__restric
 #pragma unroll
         for (int l = 0; l < M; ++l) Dr[l] = sop[OL::Dt + r * M + l];
         const T glr = sop[OL::gl + r], grr = sop[OL::gr + r];
-        const int q = r * STR;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             T s = T(0);
 #pragma unroll
             for (int l = 0; l < M; ++l) s = fma(Dr[l], F[i][l], s);
-            const T cf = fma(glr, FIm[1 + i], fma(grr, FIp[1 + i], s));
-            if constexpr (XR) ctb[1 + i][r] = cf;
-            else sCd[(1 + i) * NS + base + q] = cf;
+            ctb[1 + i][r] = fma(glr, FIm[1 + i], fma(grr, FIp[1 + i], s));
         }
     };
-    // with XR the row index selects registers, so the loop is unrolled;
-    // otherwise it stays rolled (fewer live registers)
-    if constexpr (XR || !LinesRolled<P, T>::value) {
+    // the row index selects registers, so the loop is unrolled
 #pragma unroll
-        for (int r = 0; r < M; ++r) rowF(r);
-    } else {
-#pragma unroll 1
-        for (int r = 0; r < M; ++r) rowF(r);
-    }
+    for (int r = 0; r < M; ++r) rowF(r);
 }
 
 template <int P, typename T, int D>
@@ -1680,11 +1765,11 @@ __device__ __forceinline__ void lt_velocities(const T *__restrict__ Ut, int L, T
     for (int ia = 0; ia < 3; ++ia) line_load<M, STR>(Ue + (1 + ia) * NS, X[ia]);
 }
 
-template <int P, typename T, int D, bool XR>
+template <int P, typename T, int D>
 __device__ __forceinline__ void lt_derivs(T *__restrict__ Ut, const T *__restrict__ sop,
                                           const T (&X)[3][P + 1], const T (&FIm)[NTR],
                                           const T (&FIp)[NTR], const Consts<T> &c, int L,
-                                          T *__restrict__ sCd, T (&ctb)[4][P + 1])
+                                          T (&ctb)[4][P + 1])
 {
     constexpr int M = P + 1, NS = M * M * M;
     constexpr int STR = D == 0 ? 1 : (D == 1 ? M : M * M);
@@ -1713,29 +1798,10 @@ __device__ __forceinline__ void lt_derivs(T *__restrict__ Ut, const T *__restric
             *sq = c.invT * fma(c.inv_det, gv, -*sq);
             if (va == D) pc = fma(c.zeta, gv, fma(glr, FIm[0], grr * FIp[0]));
         }
-        if constexpr (XR) ctb[0][r] = pc;
-        else sCd[base + q] = pc;
+        ctb[0][r] = pc;
     };
-    if constexpr (XR || !LinesRolled<P, T>::value) {
 #pragma unroll
-        for (int r = 0; r < M; ++r) rowV(r);
-    } else {
-#pragma unroll 1
-        for (int r = 0; r < M; ++r) rowV(r);
-    }
-}
-
-// The three phases in a row.
-template <int P, typename T, int D, bool XR>
-__device__ __forceinline__ void line_task(T *__restrict__ Ut, const T *__restrict__ sop,
-                                          const T (&othm)[NTR], const T (&othp)[NTR],
-                                          const Consts<T> &c, int L, T *__restrict__ sCd,
-                                          T (&ctb)[4][P + 1])
-{
-    T FIm[NTR], FIp[NTR], X[3][P + 1];
-    lt_fluxes<P, T, D, XR>(Ut, sop, othm, othp, c, L, sCd, ctb, FIm, FIp);
-    lt_velocities<P, T, D>(Ut, L, X);
-    lt_derivs<P, T, D, XR>(Ut, sop, X, FIm, FIp, c, L, sCd, ctb);
+    for (int r = 0; r < M; ++r) rowV(r);
 }
 
 // The face trace of a neighbour element, from its state Un (global memory or
@@ -1761,365 +1827,375 @@ __device__ __forceinline__ void nbr_trace(const T *__restrict__ Un, int L, const
     }
 }
 
-// Whether the halo form's stage-epilogue kernel loops over batches with a grid
-// bounded by the partial sums or takes one batch per workgroup.  The loop
-// holds 20-50 more VGPRs (a wave of occupancy at p = 2-5) but saves workgroup
-// launches where batches are small; measured per order and precision on the
-// dual pseudo-step.
-#ifndef FR_SL1_D
-#define FR_SL1_D 1
-#endif
-#ifndef FR_SL2_D
-#define FR_SL2_D 0
-#endif
-#ifndef FR_SL3_D
-#define FR_SL3_D 0
-#endif
-#ifndef FR_SL4_D
-#define FR_SL4_D 0
-#endif
-#ifndef FR_SL5_D
-#define FR_SL5_D 0
-#endif
-#ifndef FR_SL6_D
-#define FR_SL6_D 1
-#endif
-#ifndef FR_SL1_F
-#define FR_SL1_F 1
-#endif
-#ifndef FR_SL2_F
-#define FR_SL2_F 0
-#endif
-#ifndef FR_SL3_F
-#define FR_SL3_F 0
-#endif
-#ifndef FR_SL4_F
-#define FR_SL4_F 0
-#endif
-#ifndef FR_SL5_F
-#define FR_SL5_F 1
-#endif
-#ifndef FR_SL6_F
-#define FR_SL6_F 1
-#endif
-template <int P, typename T> struct StageLoop;
-#define FR_SLOOP(PP, TT, S) \
-    template <> struct StageLoop<PP, TT> { static constexpr bool value = FR_SL##PP##_##S != 0; };
-FR_SLOOP(1, double, D)
-FR_SLOOP(2, double, D)
-FR_SLOOP(3, double, D)
-FR_SLOOP(4, double, D)
-FR_SLOOP(5, double, D)
-FR_SLOOP(6, double, D)
-FR_SLOOP(1, float, F)
-FR_SLOOP(2, float, F)
-FR_SLOOP(3, float, F)
-FR_SLOOP(4, float, F)
-FR_SLOOP(5, float, F)
-FR_SLOOP(6, float, F)
-#undef FR_SLOOP
+// Both neighbours' traces on a line: as two calls of nbr_trace, with the plus
+// neighbour's loads issued while the minus neighbour's values are summed (the
+// loads of one neighbour, 7 m values, are in flight at any time).
+template <int P, typename T, int D>
+__device__ __forceinline__ void nbr_trace_pair(const T *__restrict__ Um, const T *__restrict__ Up, int L,
+                                               const T *__restrict__ lp, const T *__restrict__ lm,
+                                               T (&outm)[NTR], T (&outp)[NTR])
+{
+    constexpr int M = P + 1, NS = M * M * M;
+    constexpr int STR = D == 0 ? 1 : (D == 1 ? M : M * M);
+    const int base = lt_base<P, T, D>(L);
+    T x[2 * NTR][M];
+    auto request = [&](int k) {
+        const int cc = k % NTR;
+        const T *X = (k < NTR ? Um : Up) + base + (cc < 4 ? cc : 4 + 3 * (cc - 4) + D) * NS;
+#pragma unroll
+        for (int l = 0; l < M; ++l) x[k][l] = X[l * STR];
+    };
+#pragma unroll
+    for (int k = 0; k < NTR; ++k) request(k);
+#pragma unroll
+    for (int k = 0; k < 2 * NTR; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
+        const T *lf = k < NTR ? lp : lm;
+        T acc = T(0);
+#pragma unroll
+        for (int l = 0; l < M; ++l) acc = fma(lf[l], x[k][l], acc);
+        if (k < NTR) outm[k] = acc;
+        else outp[k - NTR] = acc;
+        if (k + NTR < 2 * NTR) request(k + NTR);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
 
-// Values per thread whose global operands the halo form's stage epilogue
-// requests at once, per order and precision (as stage_chunk for the point
-// form; measured: 16 spills, 1 leaves too few loads in flight).
-// FR_LSTG_CHUNK overrides the table.
-template <int P, typename T>
+// What a k_lines kernel does with its residual: write it, or apply an RK
+// stage update, the last one of a step or another, with its global accesses
+// marked nontemporal (STG_STREAM) or not.
+enum { STG_NONE = 0, STG_MID = 1, STG_LAST = 2, STG_STREAM = 4 };
+
+// Largest state array (double, bytes) whose stage updates use plain accesses:
+// the step's arrays (three to five of that size) then stay in the 256 MB
+// memory-side cache for the next stage.  RK4 steps with nontemporal against
+// plain accesses: p = 4 in single precision on 16^3 hexes (53 MB) 220 and 165 us,
+// p = 1 in double on 32^3 (27 MB) 107 and 96, p = 2 on 32^3 (92 MB) 367 and 359;
+// p = 3 on 32^3 (218 MB) 710 and 757, on 64^3 5.66 and 5.86 ms.
+constexpr size_t STAGE_KEEP_BYTES = (size_t)96 << 20;
+
+// Units (pairs of values of 64 lanes) whose global operands a wave of the halo
+// form's stage epilogue requests at once, per order, precision and kind of
+// stage (measured on the order-sweep lattices).  Each further round costs a
+// memory latency (p = 3 in double, last stage: 2.41 ms with three rounds of 4
+// units, 1.81 with two of 5), each unit registers, and from a point on a wave of
+// occupancy (6 units: 3.61 ms).  FR_STG_MID and FR_STG_END override the tables.
+template <int P, typename T, bool LAST>
 constexpr int line_stage_chunk()
 {
-#ifdef FR_LSTG_CHUNK
-    return FR_LSTG_CHUNK;
+    constexpr int md[PMAX + 1] = {0, 5, 5, 5, 1, 1, 1}, ld[PMAX + 1] = {0, 2, 3, 5, 6, 4, 2};
+    constexpr int mf[PMAX + 1] = {0, 6, 3, 3, 3, 5, 5}, lf[PMAX + 1] = {0, 2, 2, 2, 2, 2, 2};
+#if defined(FR_STG_MID) && defined(FR_STG_END)
+    return LAST ? FR_STG_END : FR_STG_MID;
 #else
-    constexpr int d[PMAX + 1] = {0, 8, 8, 8, 8, 8, 8};
-    constexpr int f[PMAX + 1] = {0, 8, 8, 4, 4, 8, 8};
-    return sizeof(T) == 8 ? d[P] : f[P];
+    return sizeof(T) == 8 ? (LAST ? ld[P] : md[P]) : (LAST ? lf[P] : mf[P]);
 #endif
 }
 
-template <int P, typename T, bool HALO, bool STG>
-__global__ void __launch_bounds__((LinesShape<P, T>::NT))
-    __attribute__((amdgpu_waves_per_eu(STG ? 1 : LinesShape<P, T>::WPE, 8)))
-    k_lines(const T *__restrict__ U, const T *__restrict__ TR, T *__restrict__ R,
-            const T *__restrict__ ops0, Consts<T> c, int nx, int ny, int nz, StageSpec sp)
+// Bricks of elements for the line forms.  A workgroup takes bx * by * bz
+// elements (at most LinesShape::E), neighbours of each other in the lattice, so
+// that the faces between them are formed from the tile; bricks at the lattice's
+// upper ends may stick out of it (those slots idle).
+//
+// Division of n < 2^31 by a number fixed on the host: n / d = n m >> s with
+// 2^(s - 32) < d <= 2^(s - 31), m = ceil(2^s / d) (the excess of m d over 2^s is
+// below 2^(s - 31), too little to reach the next quotient).
+struct FastDiv {
+    uint32_t m;
+    int s;
+    __device__ __forceinline__ unsigned operator()(unsigned n) const
+    {
+        return (unsigned)(((uint64_t)n * m) >> s);
+    }
+};
+struct Bricks {
+    int bx, by, bz;        // elements of a brick along x, y, z
+    int mx, mxy;           // ceil(2^16 / bx), ceil(2^16 / (bx by)): n / bx = n mx >> 16 for n < 256
+    int gx, gy;            // bricks of the lattice along x, y
+    FastDiv by_gx, by_gy;
+    unsigned nb;           // bricks of the lattice
+    unsigned chunk;        // bricks of an XCD's share of a group (brick_of)
+    FastDiv by_group;      // by 8 chunk
+};
+
+// Elements of the brick (slot coordinates sx, sy, sz, lattice element e; e < 0:
+// slot not in use).
+struct BrickSlot {
+    int sx, sy, sz, e;
+};
+__device__ __forceinline__ BrickSlot brick_slot(const Bricks &g, int s, int cx, int cy, int cz,
+                                                int nx, int ny, int nz)
 {
-    const int ne = nx * ny * nz;
+    BrickSlot r;
+    r.sz = (s * g.mxy) >> 16;
+    const int q = s - r.sz * (g.bx * g.by);
+    r.sy = (q * g.mx) >> 16;
+    r.sx = q - r.sy * g.bx;
+    const int x = cx + r.sx, y = cy + r.sy, z = cz + r.sz;
+    r.e = r.sz < g.bz && x < nx && y < ny && z < nz ? x + nx * (y + ny * z) : -1;
+    return r;
+}
+
+// Workgroup b's brick, or -1.  Consecutive workgroups go to the eight XCDs in
+// turn, each with an L2 of its own.  A group of 8 g.chunk bricks (one layer of
+// the lattice along z) is dealt out so that every XCD works on a contiguous
+// eighth of it: y neighbours then share an L2, and all XCDs stay on one compact
+// front of the lattice, whose last layer the memory-side cache still holds when
+// the next one reads its z neighbours.
+__device__ __forceinline__ int brick_of(const Bricks &g, unsigned b)
+{
+    const unsigned first = g.by_group(b) * 8 * g.chunk, r = b - first;
+    if (first >= g.nb) return -1;
+    const unsigned share = min(g.chunk, (g.nb - first + 7) / 8);
+    const unsigned i = r >> 3, k = r & 7;
+    const unsigned brick = first + k * share + i;
+    return i < share && brick < g.nb ? (int)brick : -1;
+}
+
+// LDS tile of the line forms: one slot per element, 16-byte aligned.  The
+// element's block starts in its slot at the same offset from a 16-byte
+// boundary as in global memory (where an odd element may start 8 bytes, in
+// single precision 4, 8 or 12, after one), so both sides move whole aligned
+// 16-byte chunks.
+template <int P, typename T>
+struct LinesTile {
+    static constexpr int M = P + 1, RAW = NV * M * M * M, VW = 16 / sizeof(T);
+    static constexpr bool ODD = RAW % VW != 0;
+    static constexpr int CH = (RAW + (ODD ? VW - 1 : 0) + VW - 1) / VW;   // chunks of a slot
+    static constexpr int SLOT = CH * VW;
+    static constexpr int OPS = LinesLds<P, T>::OPS;
+    __device__ __forceinline__ static int off(int slot, int e)
+    {
+        return slot * SLOT + (ODD ? (int)(((unsigned)e * (unsigned)RAW) % VW) : 0);
+    }
+};
+
+// One element's block into its slot by direct loads into LDS: every wave takes
+// 64 chunks of 16 bytes at a time and waits for none of them (the caller waits
+// for vmcnt before the barrier).  lo is the block's offset in its slot; bytes
+// before the block in its first chunk belong to the previous element (lo > 0
+// only for e > 0), and the chunk that holds the block's end is read in
+// four-byte words up to it, so nothing past the state is touched.
+template <int P, typename T>
+__device__ __forceinline__ void slot_load(const T *__restrict__ src, int lo, T *slot, int unit)
+{
+    using LT = LinesTile<P, T>;
+    typedef __attribute__((address_space(1))) const void gptr;
+    typedef __attribute__((address_space(3))) void lptr;
+    const int lane = threadIdx.x & 63;
+    const int whole = (lo + LT::RAW) / LT::VW;      // chunks without the block's last, partial one
+    const T *s0 = src - lo;
+    const int c0 = unit * 64;
+    if (c0 + lane < whole)
+        __builtin_amdgcn_global_load_lds((gptr *)(s0 + (c0 + lane) * LT::VW), (lptr *)(slot + c0 * LT::VW), 16,
+                                         0, 0);
+    if constexpr (LT::ODD) {
+        const int words = ((lo + LT::RAW) % LT::VW) * (int)(sizeof(T) / 4);
+        if (unit == (LT::CH - 1) / 64 && lane < words)
+            __builtin_amdgcn_global_load_lds((gptr *)((const int *)(s0 + whole * LT::VW) + lane),
+                                             (lptr *)(slot + whole * LT::VW), 4, 0, 0);
+    }
+}
+
+// The reverse: 64 chunks of an element's slot to its block in memory.
+template <int P, typename T>
+__device__ __forceinline__ void slot_store(const T *slot, int lo, T *__restrict__ dst, int unit)
+{
+    using LT = LinesTile<P, T>;
+    using V = typename V16<T>::type;
+    const int c = unit * 64 + (threadIdx.x & 63);
+    if (c >= LT::CH) return;
+    const int v0 = c * LT::VW - lo;                 // first value of the chunk
+    if (!LT::ODD || (v0 >= 0 && v0 + LT::VW <= LT::RAW)) {
+        __builtin_nontemporal_store(reinterpret_cast<const V *>(slot)[c], reinterpret_cast<V *>(dst - lo) + c);
+    } else {
+#pragma unroll
+        for (int w = 0; w < LT::VW; ++w)
+            if (v0 + w >= 0 && v0 + w < LT::RAW) __builtin_nontemporal_store(slot[c * LT::VW + w], dst + v0 + w);
+    }
+}
+
+template <int P, typename T, bool HALO, int STG>
+__global__ void __launch_bounds__((LinesShape<P, T>::NT))
+    __attribute__((amdgpu_waves_per_eu(STG ? LinesShape<P, T>::SWPE : LinesShape<P, T>::WPE, 8)))
+    k_lines(const T *__restrict__ U, const T *__restrict__ TR, T *__restrict__ R,
+            const T *__restrict__ ops, Consts<T> c, int nx, int ny, int nz, Bricks g, StageSpec sp)
+{
     constexpr int M = P + 1, NS = M * M * M, NF = M * M;
     constexpr int E = LinesShape<P, T>::E, W = LinesShape<P, T>::W, NT = LinesShape<P, T>::NT;
-    constexpr int XR = LinesShape<P, T>::XR;
-    using LL = LinesLds<P, T>;
+    using LT = LinesTile<P, T>;
     using TL = TraceLayout<M, T>;
     using OL = OpsLayout<M>;
-    constexpr int EP = LL::EP, RAW = LL::raw;
+    constexpr int RAW = LT::RAW, UNITS = (LT::CH + 63) / 64;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    T *sop0 = reinterpret_cast<T *>(smem_raw);  // operators
-    T *sU = sop0 + LL::OPS;                      // [E][EP] state tile
-    // P and momentum parts per direction, [3][E][4][NS] (XR = 1: the x
-    // direction's stay in its lanes' registers and only y and z are here;
-    // XR = 2, 3: none here)
-    T *sC = sU + E * EP - (XR == 1 ? 4 * E * NS : 0);
+    T *sop = reinterpret_cast<T *>(smem_raw);  // operators
+    T *sU = sop + LT::OPS;                      // [E] slots of the state tile
+    const int brick = brick_of(g, blockIdx.x);
+    if (brick < 0) return;
+    const int row = g.by_gx(brick), lay = g.by_gy(row);
+    const int cx = (brick - row * g.gx) * g.bx, cy = (row - lay * g.gy) * g.by, cz = lay * g.bz;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    T opv = T(0);
+    if (threadIdx.x < OL::size) opv = ops[threadIdx.x];
+    // the state of the brick's elements into LDS
+    for (int u = wave; u < E * UNITS; u += NT / 64) {
+        const int s = u / UNITS;
+        const int e = brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+        if (e >= 0) {
+            const int lo = LT::off(0, e);
+            slot_load<P, T>(U + (int64_t)e * RAW, lo, sU + s * LT::SLOT, u - s * UNITS);
+        }
+    }
     const int d = wave / W;
     const int t = (wave - d * W) * 64 + (threadIdx.x & 63);
     const int el = t / NF, L = t - el * NF;
-    const int64_t nbt = ((int64_t)ne + E - 1) / E;
-    if (threadIdx.x < OL::size) sop0[threadIdx.x] = ops0[threadIdx.x];
-    // with STG: sum of (k*_V)^2 over this workgroup's stage updates
-    double ss = 0.0;
-    auto run_batch = [&](int64_t e0, int nel) {
-        // the operator blocks through an offset the compiler cannot see, so that
-        // a loop over batches reloads them instead of holding them in registers
-        const int oz = opaque_zero();
-        const T *sop = sop0 + oz;
-        const T *ops = ops0 + oz;
-        const bool act = el < nel;
-        const int64_t e = e0 + el;
-        // the neighbours' traces on this lane's line, requested before the state:
-        // from the trace array, or with HALO from the neighbours' own states (from
-        // global memory for a neighbour outside the batch, from the tile after it
-        // is loaded otherwise)
-        T othm[NTR], othp[NTR];
-        int64_t nbm = 0, nbp = 0;
-        bool inm = false, inp = false;
-        if (act) {
-            if constexpr (HALO) {
-                nbm = neighbour(e, 2 * d, nx, ny, nz);
-                nbp = neighbour(e, 2 * d + 1, nx, ny, nz);
-                inm = nbm >= e0 && nbm < e0 + nel;
-                inp = nbp >= e0 && nbp < e0 + nel;
-                auto from_global = [&](auto dc) {
-                    constexpr int DD = decltype(dc)::value;
-                    if (!inm) nbr_trace<P, T, DD>(U + nbm * RAW, L, ops + OL::lp, othm);
-                    if (!inp) nbr_trace<P, T, DD>(U + nbp * RAW, L, ops + OL::lm, othp);
-                };
-                if (d == 0) from_global(Dir<0>{});
-                else if (d == 1) from_global(Dir<1>{});
-                else from_global(Dir<2>{});
-            } else {
-                const T *tm = TR + ((int64_t)(2 * d) * ne + e) * TL::CHP + L;
-                const T *tp = TR + ((int64_t)(2 * d + 1) * ne + e) * TL::CHP + L;
-#pragma unroll
-                for (int cc = 0; cc < NTR; ++cc) {
-                    othm[cc] = __builtin_nontemporal_load(tm + cc * NF);
-                    othp[cc] = __builtin_nontemporal_load(tp + cc * NF);
-                }
-            }
-        }
-        // the batch's state block into LDS
-        tile_load<P, T, NT>(U + e0 * RAW, sU, nel);
-        __syncthreads();
+    const BrickSlot me = brick_slot(g, el, cx, cy, cz, nx, ny, nz);
+    const bool act = el < E && me.e >= 0;
+    // the neighbours' traces on this lane's line: from the trace array, or with
+    // HALO from the neighbours' own states (from global memory for a neighbour
+    // outside the brick, from the tile after it is loaded otherwise)
+    T othm[NTR], othp[NTR];
+    int offm = -1, offp = -1;   // a neighbour inside the brick: its block in the tile
+    if (act) {
         if constexpr (HALO) {
-            if (act && (inm || inp)) {
-                auto from_tile = [&](auto dc) {
-                    constexpr int DD = decltype(dc)::value;
-                    if (inm) nbr_trace<P, T, DD>(sU + (nbm - e0) * EP, L, sop + OL::lp, othm);
-                    if (inp) nbr_trace<P, T, DD>(sU + (nbp - e0) * EP, L, sop + OL::lm, othp);
-                };
-                if (d == 0) from_tile(Dir<0>{});
-                else if (d == 1) from_tile(Dir<1>{});
-                else from_tile(Dir<2>{});
-            }
-            // a neighbour's S_ad is replaced by its auxiliary residual in the line
-            // task; with several waves per direction that lane may be in another
-            // wave, so every wave finishes these reads first
-            if constexpr (W > 1) __syncthreads();
-        }
-        T ctb[4][M];
-        const T mid = -c.inv_det;
-        // the parts ctb[k0..k1) of this lane's line added over the tile's P and
-        // velocity values (x stores, y adds, z adds and scales by -1/det J)
-        auto add_lines = [&](auto dc, auto k0c, auto k1c) {
-            constexpr int DD = decltype(dc)::value;
-            constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
-            constexpr int STR = DD == 0 ? 1 : (DD == 1 ? M : M * M);
-            T *Ue = sU + el * EP + lt_base<P, T, DD>(L);
+            const int sd = d == 0 ? me.sx : (d == 1 ? me.sy : me.sz);
+            const int bd = d == 0 ? g.bx : (d == 1 ? g.by : g.bz);
+            const int x = sd + (d == 0 ? cx : (d == 1 ? cy : cz));
+            const int n = d == 0 ? nx : (d == 1 ? ny : nz);
+            const int ldse = d == 0 ? 1 : (d == 1 ? g.bx : g.bx * g.by);
+            const int le = d == 0 ? 1 : (d == 1 ? nx : nx * ny);
+            const int nbm = me.e + (x == 0 ? n - 1 : -1) * le;
+            const int nbp = me.e + (x + 1 == n ? 1 - n : 1) * le;
+            if (sd > 0) offm = LT::off(el - ldse, nbm);
+            if (sd + 1 < bd && x + 1 < n) offp = LT::off(el + ldse, nbp);
+            auto from_global = [&](auto dc) {
+                constexpr int DD = decltype(dc)::value;
+                const T *Um = U + (int64_t)nbm * RAW, *Up = U + (int64_t)nbp * RAW;
+                if (E == 1 || (offm < 0 && offp < 0)) {
+                    nbr_trace_pair<P, T, DD>(Um, Up, L, ops + OL::lp, ops + OL::lm, othm, othp);
+                } else if (offm < 0 || offp < 0) {
+                    // one of the two, chosen per lane, in one set of loads; the
+                    // other one is replaced from the tile
+                    const bool mi = offm < 0;
+                    T lf[M];
 #pragma unroll
-            for (int k = K0; k < K1; ++k) {
-                T o[M];
-                if constexpr (DD == 0) {
+                    for (int l = 0; l < M; ++l) lf[l] = ops[mi ? OL::lp + l : OL::lm + l];
+                    nbr_trace<P, T, DD>(mi ? Um : Up, L, lf, othm);
 #pragma unroll
-                    for (int r = 0; r < M; ++r) o[r] = ctb[k][r];
-                } else {
-                    line_load<M, STR>(Ue + k * NS, o);
-#pragma unroll
-                    for (int r = 0; r < M; ++r) o[r] = o[r] + ctb[k][r];
-                    if constexpr (DD == 2) {
-#pragma unroll
-                        for (int r = 0; r < M; ++r) o[r] = mid * o[r];
-                    }
+                    for (int cc = 0; cc < NTR; ++cc) othp[cc] = othm[cc];
                 }
-                line_put<M, STR>(Ue + k * NS, o);
-            }
-        };
-        if constexpr (XR == 3) {
-            // the momentum parts are summed between the two halves of the line
-            // task, once every lane has read the tile's P and velocities, and the
-            // P parts after it: the fluxes' and the velocities' parts are never
-            // held in registers together
-            T FIm[NTR], FIp[NTR], X[3][M];
-            T *Ut = sU + el * EP;
-            if (act) {
-                auto ph1 = [&](auto dc) {
-                    constexpr int DD = decltype(dc)::value;
-                    lt_fluxes<P, T, DD, true>(Ut, sop, othm, othp, c, L, nullptr, ctb, FIm, FIp);
-                    lt_velocities<P, T, DD>(Ut, L, X);
-                };
-                if (d == 0) ph1(Dir<0>{});
-                else if (d == 1) ph1(Dir<1>{});
-                else ph1(Dir<2>{});
-            }
-            __syncthreads();
-            if (act && d == 0) add_lines(Dir<0>{}, Dir<1>{}, Dir<4>{});
-            __syncthreads();
-            if (act && d == 1) add_lines(Dir<1>{}, Dir<1>{}, Dir<4>{});
-            __syncthreads();
-            if (act && d == 2) add_lines(Dir<2>{}, Dir<1>{}, Dir<4>{});
-            if (act) {
-                if (d == 0) lt_derivs<P, T, 0, true>(Ut, sop, X, FIm, FIp, c, L, nullptr, ctb);
-                else if (d == 1) lt_derivs<P, T, 1, true>(Ut, sop, X, FIm, FIp, c, L, nullptr, ctb);
-                else lt_derivs<P, T, 2, true>(Ut, sop, X, FIm, FIp, c, L, nullptr, ctb);
-            }
-            if (act && d == 0) add_lines(Dir<0>{}, Dir<0>{}, Dir<1>{});
-            __syncthreads();
-            if (act && d == 1) add_lines(Dir<1>{}, Dir<0>{}, Dir<1>{});
-            __syncthreads();
-            if (act && d == 2) add_lines(Dir<2>{}, Dir<0>{}, Dir<1>{});
+            };
+            if (d == 0) from_global(Dir<0>{});
+            else if (d == 1) from_global(Dir<1>{});
+            else from_global(Dir<2>{});
         } else {
-            if (act) {
-                T *Ut = sU + el * EP;
-                T *sCd = sC + ((d * E + el) * 4) * NS;
-                if (d == 0) line_task<P, T, 0, (XR >= 1)>(Ut, sop, othm, othp, c, L, sCd, ctb);
-                else if (d == 1) line_task<P, T, 1, (XR == 2)>(Ut, sop, othm, othp, c, L, sCd, ctb);
-                else line_task<P, T, 2, (XR == 2)>(Ut, sop, othm, othp, c, L, sCd, ctb);
+            const int64_t ne = (int64_t)nx * ny * nz;
+            const T *tm = TR + ((int64_t)(2 * d) * ne + me.e) * TL::CHP + L;
+            const T *tp = TR + ((int64_t)(2 * d + 1) * ne + me.e) * TL::CHP + L;
+#pragma unroll
+            for (int cc = 0; cc < NTR; ++cc) {
+                othm[cc] = __builtin_nontemporal_load(tm + cc * NF);
+                othp[cc] = __builtin_nontemporal_load(tp + cc * NF);
             }
-            __syncthreads();
         }
-        // R of the batch: P and momentum summed over the three directions in the
-        // order x, y, z and scaled by -1/det J, the auxiliary residuals from the
-        // tile.  Without STG it goes to R; with STG it stays in the tile for the
-        // stage update.
-        if constexpr (XR == 3) {
-            if constexpr (!STG) {
-                __syncthreads();
-                tile_store<P, T, NT>(sU, R + e0 * RAW, nel);
-            }
-        } else if constexpr (XR == 2) {
-            // summed over the tile's P and velocity values, one direction after
-            // the other
-            if (act && d == 0) add_lines(Dir<0>{}, Dir<0>{}, Dir<4>{});
-            __syncthreads();
-            if (act && d == 1) add_lines(Dir<1>{}, Dir<0>{}, Dir<4>{});
-            __syncthreads();
-            if (act && d == 2) add_lines(Dir<2>{}, Dir<0>{}, Dir<4>{});
-            if constexpr (!STG) {
-                __syncthreads();
-                tile_store<P, T, NT>(sU, R + e0 * RAW, nel);
-            }
-        } else if constexpr (XR == 1) {
-            // x lanes: their own parts plus those of y and z at the x-line's points
-            if (act && d == 0) {
-                const T *cy = sC + ((E + el) * 4) * NS + M * L;
-                const T *cz = sC + ((2 * E + el) * 4) * NS + M * L;
-                T *Re = R + e * (NV * NS) + M * L;
+    }
+    if (threadIdx.x < OL::size) sop[threadIdx.x] = opv;
+    // the direct loads into LDS have arrived (their count is not tracked by the
+    // barrier)
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if constexpr (HALO && E > 1) {
+        if (offm >= 0 || offp >= 0) {
+            auto from_tile = [&](auto dc) {
+                constexpr int DD = decltype(dc)::value;
+                if (offm >= 0) nbr_trace<P, T, DD>(sU + offm, L, sop + OL::lp, othm);
+                if (offp >= 0) nbr_trace<P, T, DD>(sU + offp, L, sop + OL::lm, othp);
+            };
+            if (d == 0) from_tile(Dir<0>{});
+            else if (d == 1) from_tile(Dir<1>{});
+            else from_tile(Dir<2>{});
+        }
+    }
+    T *Ut = sU + (act ? LT::off(el, me.e) : 0);
+    T ctb[4][M];
+    const T mid = -c.inv_det;
+    // the parts ctb[k0..k1) of this lane's line added over the tile's P and
+    // velocity values (x stores, y adds, z adds and scales by -1/det J)
+    auto add_lines = [&](auto dc, auto k0c, auto k1c) {
+        constexpr int DD = decltype(dc)::value;
+        constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
+        constexpr int STR = DD == 0 ? 1 : (DD == 1 ? M : M * M);
+        T *Ue = Ut + lt_base<P, T, DD>(L);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    T o[M];
+        for (int k = K0; k < K1; ++k) {
+            T o[M];
+            if constexpr (DD == 0) {
 #pragma unroll
-                    for (int r = 0; r < M; ++r) o[r] = mid * ((ctb[k][r] + cy[k * NS + r]) + cz[k * NS + r]);
-                    if constexpr (STG) line_put<M, 1>(sU + el * EP + M * L + k * NS, o);
-                    else line_store<M, 1>(Re + k * NS, o);
-                }
-            }
-            if constexpr (!STG) {
-                // every thread: the auxiliary residuals from the tile
-                T *dst = R + e0 * RAW;
-                constexpr int A0 = 4 * NS, NA = 9 * NS;
-                if constexpr (LL::VEC && (A0 * sizeof(T)) % 16 == 0) {
-                    using V = typename V16<T>::type;
-                    constexpr int VW = 16 / sizeof(T), CPE = NA / VW;
-                    const int nch = nel * CPE;
-#pragma unroll 4
-                    for (int k = threadIdx.x; k < nch; k += NT) {
-                        const int ek = k / CPE, o = k - ek * CPE;
-                        __builtin_nontemporal_store(reinterpret_cast<const V *>(sU + ek * EP + A0)[o],
-                                                    reinterpret_cast<V *>(dst + ek * RAW + A0) + o);
-                    }
-                } else {
-                    const int nv = nel * NA;
-#pragma unroll 4
-                    for (int k = threadIdx.x; k < nv; k += NT) {
-                        const int ek = k / NA, o = k - ek * NA;
-                        __builtin_nontemporal_store(sU[ek * EP + A0 + o], dst + ek * RAW + A0 + o);
-                    }
-                }
-            }
-        } else {
-            // one pass over the batch: the three directions' parts from their
-            // slots, the auxiliary residuals from the tile
-            T *dst = R + e0 * RAW;
-            if constexpr (LL::VEC) {
-                using V = typename V16<T>::type;
-                constexpr int VW = 16 / sizeof(T), CPE = RAW / VW, C4 = 4 * NS / VW;
-                static_assert((4 * NS) % VW == 0, "P and momentum in whole chunks");
-                const int nch = nel * CPE;
-#pragma unroll 4
-                for (int k = threadIdx.x; k < nch; k += NT) {
-                    const int ek = k / CPE, o = k - ek * CPE;
-                    V x;
-                    if (o < C4) {
-                        const V *cx = reinterpret_cast<const V *>(sC + (ek * 4) * NS) + o;
-                        const V *cy = reinterpret_cast<const V *>(sC + ((E + ek) * 4) * NS) + o;
-                        const V *cz = reinterpret_cast<const V *>(sC + ((2 * E + ek) * 4) * NS) + o;
-                        const V vx = *cx, vy = *cy, vz = *cz;
-#pragma unroll
-                        for (int w = 0; w < VW; ++w) x[w] = mid * ((vx[w] + vy[w]) + vz[w]);
-                        if constexpr (STG) reinterpret_cast<V *>(sU + ek * EP)[o] = x;
-                    } else {
-                        x = reinterpret_cast<const V *>(sU + ek * EP)[o];
-                    }
-                    if constexpr (!STG) __builtin_nontemporal_store(x, reinterpret_cast<V *>(dst) + k);
-                }
+                for (int r = 0; r < M; ++r) o[r] = ctb[k][r];
             } else {
-                const int nv = nel * RAW;
-#pragma unroll 4
-                for (int k = threadIdx.x; k < nv; k += NT) {
-                    const int ek = k / RAW, o = k - ek * RAW;
-                    T x;
-                    if (o < 4 * NS) {
-                        const T *cx = sC + (ek * 4) * NS + o;
-                        x = mid * ((cx[0] + cx[E * 4 * NS]) + cx[2 * E * 4 * NS]);
-                        if constexpr (STG) sU[ek * EP + o] = x;
-                    } else {
-                        x = sU[ek * EP + o];
-                    }
-                    if constexpr (!STG) __builtin_nontemporal_store(x, dst + k);
+                line_load<M, STR>(Ue + k * NS, o);
+#pragma unroll
+                for (int r = 0; r < M; ++r) o[r] = o[r] + ctb[k][r];
+                if constexpr (DD == 2) {
+#pragma unroll
+                    for (int r = 0; r < M; ++r) o[r] = mid * o[r];
                 }
             }
-        }
-        if constexpr (STG) {
-            // ---- the RK stage update of the batch from its residual in the tile
-            constexpr int J = (E * RAW + NT - 1) / NT;
-            constexpr int C = line_stage_chunk<P, T>() < J ? line_stage_chunk<P, T>() : J;
-            __syncthreads();
-            stage_update_batch<J, C, NS, T, true>(
-                sp, [&](unsigned q) -> T & { return sU[(q / RAW) * EP + q % RAW]; }, threadIdx.x, NT,
-                (unsigned)nel * RAW, e0, ss);
+            line_put<M, STR>(Ue + k * NS, o);
         }
     };
-    auto batch_at = [&](int64_t bt) {
-        const int64_t e0 = bt * E;
-        run_batch(e0, (int)min((int64_t)E, (int64_t)ne - e0));
-    };
-    if constexpr (STG && StageLoop<P, T>::value) {
-        // the stage epilogue's grid bounded by its partial sums: a workgroup
-        // may take several batches
-        for (int64_t bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
-            if (bt != (int64_t)blockIdx.x) __syncthreads();  // the tile is free again
-            batch_at(bt);
+    // the momentum parts are summed between the two halves of the line task,
+    // once every lane has read the tile's P and velocities, and the P parts
+    // after it: the fluxes' and the velocities' parts are never held in
+    // registers together
+    T FIm[NTR], FIp[NTR], X[3][M];
+    if (act) {
+        auto ph1 = [&](auto dc) {
+            constexpr int DD = decltype(dc)::value;
+            lt_fluxes<P, T, DD>(Ut, sop, othm, othp, c, L, ctb, FIm, FIp);
+            lt_velocities<P, T, DD>(Ut, L, X);
+        };
+        if (d == 0) ph1(Dir<0>{});
+        else if (d == 1) ph1(Dir<1>{});
+        else ph1(Dir<2>{});
+    }
+    __syncthreads();
+    if (act && d == 0) add_lines(Dir<0>{}, Dir<1>{}, Dir<4>{});
+    __syncthreads();
+    if (act && d == 1) add_lines(Dir<1>{}, Dir<1>{}, Dir<4>{});
+    __syncthreads();
+    if (act && d == 2) add_lines(Dir<2>{}, Dir<1>{}, Dir<4>{});
+    if (act) {
+        if (d == 0) lt_derivs<P, T, 0>(Ut, sop, X, FIm, FIp, c, L, ctb);
+        else if (d == 1) lt_derivs<P, T, 1>(Ut, sop, X, FIm, FIp, c, L, ctb);
+        else lt_derivs<P, T, 2>(Ut, sop, X, FIm, FIp, c, L, ctb);
+    }
+    if (act && d == 0) add_lines(Dir<0>{}, Dir<0>{}, Dir<1>{});
+    __syncthreads();
+    if (act && d == 1) add_lines(Dir<1>{}, Dir<0>{}, Dir<1>{});
+    __syncthreads();
+    if (act && d == 2) add_lines(Dir<2>{}, Dir<0>{}, Dir<1>{});
+    __syncthreads();
+    // the tile holds R of the brick
+    if constexpr (STG == STG_NONE) {
+        for (int u = wave; u < E * UNITS; u += NT / 64) {
+            const int s = u / UNITS;
+            const int e = brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+            if (e >= 0) slot_store<P, T>(sU + s * LT::SLOT, LT::off(0, e), R + (int64_t)e * RAW, u - s * UNITS);
         }
     } else {
-        // one batch per workgroup (the partial sums take one slot per batch)
-        batch_at(blockIdx.x);
-    }
-    if constexpr (STG) {
+        // the RK stage update of the brick from its residual in the tile; ss:
+        // this thread's sum of (k*_V)^2
+        double ss = 0.0;
+        constexpr bool LAST = (STG & STG_LAST) != 0, NTS = (STG & STG_STREAM) != 0;
+        StageSlots<LAST, NTS, E, NT / 64, line_stage_chunk<P, T, LAST>(), NS, T> stage;
+        auto elem = [&](int s) { return brick_slot(g, s, cx, cy, cz, nx, ny, nz).e; };
+        auto tile = [&](int s, int e) -> const T * { return sU + LT::off(s, e); };
+#pragma unroll 1
+        for (int u0 = wave; u0 < E * stage.UN; u0 += stage.STEP) {
+            stage.request(sp, elem, u0);
+            stage.apply(sp, elem, tile, u0, ss);
+        }
         if (sp.partial) {
             // fixed-order workgroup sum: wave butterfly, then the waves in order
             __shared__ double red[NT / 64];
@@ -2130,7 +2206,7 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
             if (threadIdx.x == 0) {
                 double tsum = 0.0;
                 for (int w = 0; w < NT / 64; ++w) tsum += red[w];
-                sp.partial[blockIdx.x] = tsum;
+                sp.partial[brick] = tsum;
             }
         }
     }
@@ -2358,6 +2434,53 @@ __global__ void __launch_bounds__(FR_TLNT)
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
+// The bricks a lattice is cut into for a kernel whose workgroups hold at most E
+// elements: the shape with the least cost, bricks (4 E + pairs of outer faces)
+// (a brick costs its workgroup's time whether its slots are in use or not, and
+// the neighbours' traces on its outer faces come from memory; at p = 1 on 128^3
+// hexes 4x4x1 takes 0.88 ms and 16x1x1 0.93 in double, 0.52 and 0.60 in single
+// precision), the longest along x where it is equal (at p = 4 on 51^3 hexes 2x1x1
+// takes 0.98 ms and 1x2x1 1.02).  A lattice of up to 256 elements (one
+// for each CU; 512 in single precision, whose bricks are half as large) gets
+// one-element bricks and one of up to E times that smaller ones in proportion:
+// such a call takes one workgroup's latency, which grows with its brick (RK4 step
+// at p = 3 in double on 6^3 hexes: 44 us with one-element bricks, 56 with four).
+FastDiv fast_div(uint32_t d)
+{
+    FastDiv f{0, 31};
+    while (f.s < 62 && (uint64_t)1 << (f.s - 31) < d) ++f.s;
+    f.m = (uint32_t)((((uint64_t)1 << f.s) + d - 1) / d);
+    return f;
+}
+
+Bricks bricks_for(int E, int esize, int nx, int ny, int nz)
+{
+    const int64_t ne = (int64_t)nx * ny * nz;
+    const int few = esize == 8 ? 256 : 512;
+    const int most = (int)std::min<int64_t>(E, (ne + few - 1) / few);
+    Bricks g{};
+    double best = 0.0;
+    for (int bx = most; bx >= 1; --bx)
+        for (int by = 1; bx * by <= most; ++by)
+            for (int bz = 1; bx * by * bz <= most; ++bz) {
+                const double nb = (double)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
+                const double cost = nb * (4 * E + bx * by + by * bz + bz * bx);
+                if (g.bx && cost >= best) continue;
+                best = cost;
+                g.bx = bx, g.by = by, g.bz = bz;
+            }
+    g.mx = (65536 + g.bx - 1) / g.bx;
+    g.mxy = (65536 + g.bx * g.by - 1) / (g.bx * g.by);
+    g.gx = (nx + g.bx - 1) / g.bx;
+    g.gy = (ny + g.by - 1) / g.by;
+    g.nb = (unsigned)g.gx * (unsigned)g.gy * (unsigned)((nz + g.bz - 1) / g.bz);
+    g.chunk = (unsigned)(((int64_t)g.gx * g.gy + 7) / 8);
+    g.by_gx = fast_div(g.gx);
+    g.by_gy = fast_div(g.gy);
+    g.by_group = fast_div(8 * g.chunk);
+    return g;
+}
+
 template <int P, typename T, bool DIAG, bool MF>
 int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, T *TR,
                const T *ops, const Consts<T> &c, hipStream_t s, bool prof)
@@ -2458,13 +2581,19 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
     }
     if (lines) {
         constexpr int LE = LinesShape<P, T>::E, LNT = LinesShape<P, T>::NT;
-        const size_t lds_li = (size_t)LinesLds<P, T>::values(LE, LinesShape<P, T>::XR) * sizeof(T);
-        const int64_t nb = ((int64_t)ne + LE - 1) / LE;
+        using LT = LinesTile<P, T>;
+        constexpr size_t lds_li = ((size_t)LT::OPS + (size_t)LE * LT::SLOT) * sizeof(T);
+        static_assert(lds_li <= 160 * 1024, "LDS");
+        const Bricks g = bricks_for(LE, sizeof(T), pl->nx, pl->ny, pl->nz);
+        const unsigned blocks = (g.nb + 7) / 8 * 8;
         int &set = pl->lines_attr[0][P][sizeof(T) == 8];
         if (!set) {
-            for (const void *fn : {(const void *)k_lines<P, T, false, false>,
-                                   (const void *)k_lines<P, T, true, false>,
-                                   (const void *)k_lines<P, T, true, true>})
+            for (const void *fn : {(const void *)k_lines<P, T, false, STG_NONE>,
+                                   (const void *)k_lines<P, T, true, STG_NONE>,
+                                   (const void *)k_lines<P, T, true, STG_MID>,
+                                   (const void *)k_lines<P, T, true, STG_LAST>,
+                                   (const void *)k_lines<P, T, true, STG_MID | STG_STREAM>,
+                                   (const void *)k_lines<P, T, true, STG_LAST | STG_STREAM>})
                 if (int rc = check_hip(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                            (int)lds_li),
                                        "hipFuncSetAttribute"))
@@ -2474,20 +2603,22 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
         ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
         if constexpr (DIAG) {
             if (sp) {
-                // one partial norm sum per workgroup (the caller sizes the
-                // partial sums by stage_partials)
-                const unsigned g =
-                    (unsigned)(StageLoop<P, T>::value ? std::min<int64_t>(nb, MAX_PARTIALS) : nb);
-                if (nparts) *nparts = (int)g;
-                hipLaunchKernelGGL((k_lines<P, T, true, true>), dim3(g), dim3(LNT), lds_li, s, U,
-                                   (const T *)nullptr, (T *)nullptr, ops, c, pl->nx, pl->ny, pl->nz,
-                                   *sp);
+                // one partial norm sum per brick (the caller sizes the partial
+                // sums by stage_partials)
+                if (nparts) *nparts = (int)g.nb;
+                const bool keep = (size_t)ne * LT::RAW * sizeof(double) <= STAGE_KEEP_BYTES;
+                const auto kernel =
+                    keep ? (sp->last ? k_lines<P, T, true, STG_LAST> : k_lines<P, T, true, STG_MID>)
+                         : (sp->last ? k_lines<P, T, true, STG_LAST | STG_STREAM>
+                                     : k_lines<P, T, true, STG_MID | STG_STREAM>);
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(LNT), lds_li, s, U, (const T *)nullptr,
+                                   (T *)nullptr, ops, c, pl->nx, pl->ny, pl->nz, g, *sp);
             } else if (halo) {
-                hipLaunchKernelGGL((k_lines<P, T, true, false>), dim3((unsigned)nb), dim3(LNT), lds_li,
-                                   s, U, TR, R, ops, c, pl->nx, pl->ny, pl->nz, StageSpec{});
+                hipLaunchKernelGGL((k_lines<P, T, true, STG_NONE>), dim3(blocks), dim3(LNT), lds_li,
+                                   s, U, TR, R, ops, c, pl->nx, pl->ny, pl->nz, g, StageSpec{});
             } else {
-                hipLaunchKernelGGL((k_lines<P, T, false, false>), dim3((unsigned)nb), dim3(LNT), lds_li,
-                                   s, U, TR, R, ops, c, pl->nx, pl->ny, pl->nz, StageSpec{});
+                hipLaunchKernelGGL((k_lines<P, T, false, STG_NONE>), dim3(blocks), dim3(LNT), lds_li,
+                                   s, U, TR, R, ops, c, pl->nx, pl->ny, pl->nz, g, StageSpec{});
             }
         }
         return check_hip(hipGetLastError(), "fused residual launch");
@@ -2677,20 +2808,20 @@ int stage_path(const fr_plan *pl)
     if (residual_form(pl) != FR_FORM_HALO) return point;
     if (pl->form == FR_FORM_HALO) return FR_STAGE_HALO;
     const bool f64 = pl->precision == FR_F64;
-    auto pick = [&](auto pc) {
+    auto most = [&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        return f64 ? StageAuto<P, double>::value : StageAuto<P, float>::value;
+        return f64 ? stage_point_most<P, double>() : stage_point_most<P, float>();
     };
-    int a = FR_STAGE_HALO;
+    int m = 0;
     switch (pl->p) {
-        case 1: a = pick(Dir<1>{}); break;
-        case 2: a = pick(Dir<2>{}); break;
-        case 3: a = pick(Dir<3>{}); break;
-        case 4: a = pick(Dir<4>{}); break;
-        case 5: a = pick(Dir<5>{}); break;
-        case 6: a = pick(Dir<6>{}); break;
+        case 1: m = most(Dir<1>{}); break;
+        case 2: m = most(Dir<2>{}); break;
+        case 3: m = most(Dir<3>{}); break;
+        case 4: m = most(Dir<4>{}); break;
+        case 5: m = most(Dir<5>{}); break;
+        case 6: m = most(Dir<6>{}); break;
     }
-    return a == FR_STAGE_POINT ? point : a;
+    return pl->ne <= m ? point : FR_STAGE_HALO;
 }
 
 int stage_partials(const fr_plan *pl)
@@ -2700,9 +2831,7 @@ int stage_partials(const fr_plan *pl)
     auto pick = [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         const int E = f64 ? LinesShape<P, double>::E : LinesShape<P, float>::E;
-        const bool loop = f64 ? StageLoop<P, double>::value : StageLoop<P, float>::value;
-        const int64_t nb = (pl->ne + E - 1) / E;
-        return (int)(loop ? std::min<int64_t>(nb, MAX_PARTIALS) : nb);
+        return (int)bricks_for(E, f64 ? 8 : 4, pl->nx, pl->ny, pl->nz).nb;
     };
     switch (pl->p) {
         case 1: return pick(Dir<1>{});

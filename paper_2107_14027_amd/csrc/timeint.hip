@@ -4,7 +4,7 @@
 // reduction for the pseudo-residual norm, and polynomial extrapolation.
 // All are HBM-bound streams; each thread handles consecutive 64-bit or 32-bit
 // words of one state array so that every wave access is contiguous.
-#include "fr_internal.h"
+#include "fr_device.h"
 
 namespace fr {
 namespace {
@@ -32,53 +32,86 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
     return s;
 }
 
-// One RK4 stage of dU/dtau = k*, with k* = k - [v in V] (a s + B) when bdf,
-// plus D (a fixed source, when given):
+// k* = k - [v in V] (a s + B) when B, plus D when given; vel: a velocity value.
+__device__ __forceinline__ double pseudo_rate(double kv, const double *s, const double *B,
+                                              const double *D, double a, int64_t i, int ns, bool &vel)
+{
+    const int64_t r = i / ns, e = r / NV;
+    const int v = (int)(r - e * NV);
+    vel = v >= 1 && v <= 3;
+    if (B && vel) kv -= fma(a, s[i], B[(e * 3 + (v - 1)) * ns + (i - r * ns)]);
+    if (D) kv += D[i];
+    return kv;
+}
+
+// One RK4 stage of dU/dtau = k* for a single-precision residual k:
 //   first stage: acc = U + b k*,  else acc += b k*
-//   then the next stage state  s' = U + cnext k*  -> st64 (double) and stT (T)
-//   last stage:  U = acc + b k*, stT = (T) U
-// s (the state that produced k) is U on the first stage and st64 otherwise.
-// With norm, also writes per-block sums of (k*_V)^2 into partial[blockIdx].
-template <typename T, bool BDF, bool NORM>
-__global__ void __launch_bounds__(TB) k_stage(double *__restrict__ U, double *__restrict__ acc,
-                                              double *st64, T *stT, const T *__restrict__ k,
-                                              const double *__restrict__ B,
-                                              const double *__restrict__ D, double a, double b,
-                                              double cnext, int first, int last, int64_t n, int ns,
-                                              double *__restrict__ partial)
+//   then the next stage state  s' = U + cnext k*  -> stT (float), velocities
+//   also to st64 (double)
+//   last stage:  U = acc + b k*, stT = (float) U
+// The velocities that produced k are U's on the first stage and st64's
+// otherwise.  partial, when given, receives per-block sums of (k*_V)^2.
+__global__ void __launch_bounds__(TB) k_stage32(double *__restrict__ U, double *__restrict__ acc,
+                                                double *st64, float *stT, const float *__restrict__ k,
+                                                const double *__restrict__ B,
+                                                const double *__restrict__ D, double a, double b,
+                                                double cnext, int first, int last, int64_t n, int ns,
+                                                double *__restrict__ partial)
 {
     __shared__ double sh[TB / 64];
     double ss = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) {
-        double kv = (double)k[i];
-        bool vel = false;
-        if (BDF || NORM) {
-            const int64_t r = i / ns;
-            const int v = (int)(r % NV);
-            vel = v >= 1 && v <= 3;
-            if (BDF && vel) {
-                const double sv = first ? U[i] : st64[i];
-                const int64_t e = r / NV;
-                kv -= fma(a, sv, B[(e * 3 + (v - 1)) * ns + (i - r * ns)]);
-            }
-        }
-        if (D) kv += D[i];
-        if (NORM && vel) ss = fma(kv, kv, ss);
+        bool vel;
+        const double kv = pseudo_rate((double)k[i], first ? U : st64, B, D, a, i, ns, vel);
+        if (vel) ss = fma(kv, kv, ss);
         if (last) {
             const double un = fma(b, kv, acc[i]);
             U[i] = un;
-            if (stT) stT[i] = (T)un;
+            stT[i] = (float)un;
         } else {
             const double u = U[i];
             acc[i] = fma(b, kv, first ? u : acc[i]);
             const double sn = fma(cnext, kv, u);
-            if (st64 && (void *)st64 != (void *)stT) st64[i] = sn;
-            stT[i] = (T)sn;
+            if (st64 && vel) st64[i] = sn;
+            stT[i] = (float)sn;
         }
     }
-    if (NORM) {
+    if (partial) {
         const double s = block_sum(ss, sh);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    }
+}
+
+// The same for a double residual k, without an accumulator (rk4_last); s is
+// the state that produced k.
+//   stage 0: st = s2 = U + cnext k*          stage 1: k = s3 = U + cnext k*
+//   stage 2: st = (s2 - U) + 2 (s3 - U) with s = s3,  k = s4 = U + cnext k*
+//   stage 3: U = rk4_last(U, st, s4, b, k*) with s = s4
+// The stage states replace the residuals, so three arrays hold a step.
+__global__ void __launch_bounds__(TB) k_stage64(double *__restrict__ U, double *st, double *k,
+                                                const double *s, const double *__restrict__ B,
+                                                const double *__restrict__ D, double a, double b,
+                                                double cnext, int stage, int64_t n, int ns,
+                                                double *__restrict__ partial)
+{
+    __shared__ double sh[TB / 64];
+    double ss = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) {
+        bool vel;
+        const double kv = pseudo_rate(k[i], s, B, D, a, i, ns, vel);
+        if (vel) ss = fma(kv, kv, ss);
+        const double u = U[i];
+        if (stage == 3) {
+            U[i] = dev::rk4_last(u, st[i], s[i], b, kv);
+        } else {
+            const double sn = fma(cnext, kv, u);
+            if (stage == 2) st[i] = fma(2.0, s[i] - u, st[i] - u);
+            (stage == 0 ? st : k)[i] = sn;
+        }
+    }
+    if (partial) {
+        const double sum = block_sum(ss, sh);
+        if (threadIdx.x == 0) partial[blockIdx.x] = sum;
     }
 }
 
@@ -190,46 +223,30 @@ __global__ void __launch_bounds__(TB) k_extrap(const double *__restrict__ Un,
     }
 }
 
-template <typename T>
-int stage_dispatch(bool bdf, bool norm, double *U, double *acc, double *st64, void *stT,
-                   const void *k, const double *B, const double *D, double a, double b,
-                   double cnext, int first, int last, int64_t n, int ns, double *partial,
-                   hipStream_t s)
-{
-    const unsigned g = grid_for(n);
-    T *st = (T *)stT;
-    const T *kk = (const T *)k;
-    if (bdf && norm)
-        hipLaunchKernelGGL((k_stage<T, true, true>), dim3(g), dim3(TB), 0, s, U, acc, st64, st, kk,
-                           B, D, a, b, cnext, first, last, n, ns, partial);
-    else if (bdf)
-        hipLaunchKernelGGL((k_stage<T, true, false>), dim3(g), dim3(TB), 0, s, U, acc, st64, st,
-                           kk, B, D, a, b, cnext, first, last, n, ns, partial);
-    else if (norm)
-        hipLaunchKernelGGL((k_stage<T, false, true>), dim3(g), dim3(TB), 0, s, U, acc, st64, st,
-                           kk, B, D, a, b, cnext, first, last, n, ns, partial);
-    else
-        hipLaunchKernelGGL((k_stage<T, false, false>), dim3(g), dim3(TB), 0, s, U, acc, st64, st,
-                           kk, B, D, a, b, cnext, first, last, n, ns, partial);
-    return check_hip(hipGetLastError(), "k_stage launch");
-}
-
 }  // namespace
 
 int stage_blocks(int64_t n) { return (int)grid_for(n); }
 
-int launch_stage(fr_plan *pl, bool bdf, bool norm, double *U, double *acc, double *st64,
-                 void *stT, const void *k, const double *B, double a, double b, double cnext,
-                 int first, int last, double *partial, hipStream_t s, const double *D)
+int launch_stage32(fr_plan *pl, int stage, double *U, double *acc, double *st64, float *stT,
+                   const float *k, const double *B, const double *D, double a, double b,
+                   double cnext, double *partial, hipStream_t s)
 {
     const int64_t n = (int64_t)fr_state_len(pl);
-    const int ns = pl->m * pl->m * pl->m;
     ProfScope ps(pl, FR_K_STAGE, s);
-    if (pl->precision == FR_F64)
-        return stage_dispatch<double>(bdf, norm, U, acc, st64, stT, k, B, D, a, b, cnext, first,
-                                      last, n, ns, partial, s);
-    return stage_dispatch<float>(bdf, norm, U, acc, st64, stT, k, B, D, a, b, cnext, first, last,
-                                 n, ns, partial, s);
+    hipLaunchKernelGGL(k_stage32, dim3(grid_for(n)), dim3(TB), 0, s, U, acc, st64, stT, k, B, D, a, b,
+                       cnext, stage == 0, stage == 3, n, pl->m * pl->m * pl->m, partial);
+    return check_hip(hipGetLastError(), "k_stage32 launch");
+}
+
+int launch_stage64(fr_plan *pl, int stage, double *U, double *st, double *k, const double *sin,
+                   const double *B, const double *D, double a, double b, double cnext,
+                   double *partial, hipStream_t s)
+{
+    const int64_t n = (int64_t)fr_state_len(pl);
+    ProfScope ps(pl, FR_K_STAGE, s);
+    hipLaunchKernelGGL(k_stage64, dim3(grid_for(n)), dim3(TB), 0, s, U, st, k, sin, B, D, a, b, cnext,
+                       stage, n, pl->m * pl->m * pl->m, partial);
+    return check_hip(hipGetLastError(), "k_stage64 launch");
 }
 
 int launch_stage34(fr_plan *pl, int stage, double *U, double *acc, double *err, double *h,
