@@ -11,9 +11,11 @@
 //   u^I   = (u_L + u_R)/2 + beta (u_L - u_R)
 //   F_v^I = (F_vL + F_vR).n/2 - beta (F_vL - F_vR).n + tau (u_L - u_R)   (velocity)
 //
-// Four kernels compiled per order, every intermediate through HBM (this is
-// the unfused multi-step pipeline that hyperbolised diffusion removes); the
-// trace, gradient and residual kernels stage their elements' data in LDS:
+// One kernel (k_acm_lines, below) where the Jacobian is diagonal and beta = 1/2;
+// otherwise, and for the gradient, four kernels compiled per order, every
+// intermediate through HBM (this is the unfused multi-step pipeline that
+// hyperbolised diffusion removes); the trace, gradient and residual kernels
+// stage their elements' data in LDS:
 //   k_acm_trace   U -> face traces of P, V         utr[e][6][4][m^2]
 //   k_acm_grad    U, utr -> corrected gradient     Q[e][9][m^3]   (du_i/dx_j at 3 i + j)
 //   k_acm_common  utr, Q -> common normal flux     FI[e][3][4][m^2] (plus face of e)
@@ -23,10 +25,11 @@
 #include <algorithm>
 #include <cmath>
 
-#include "fr_internal.h"
+#include "bricks.h"
 
 namespace fr {
 namespace {
+using namespace dev;
 
 constexpr int NA = 4;
 constexpr int TB = 256;
@@ -40,7 +43,13 @@ struct AcmArgs {
     double nvec[9], nhat[9], nmag[3]; // n_d = det J J^{-T} e_d, n_d / |n_d|, |n_d|
     double inv_det, zeta, nu, beta, tau;
     int m, nx, ny, nz;
+    int diag;                         // the Jacobian is diagonal
 };
+
+// The operators k_acm_lines takes (AcmOps<m>).
+constexpr int LINE_OPS = MM * MM + 5 * MM + 2;
+
+template <int D> struct Dir { static constexpr int value = D; };
 
 __device__ __forceinline__ int line_pt(int m, int d, int a, int b, int l)
 {
@@ -253,6 +262,280 @@ __global__ void __launch_bounds__(RES_TB) k_acm_resid(const double *__restrict__
     for (int v = 0; v < NA; ++v) Re[v * ns] = -div[v] * A.inv_det;
 }
 
+// ---------------------------------------------------------------------------
+// k_acm_lines: the whole residual in one kernel, for a diagonal Jacobian and
+// beta = 1/2 (the usual LDG switch).  Along an element line of direction d
+// everything is then one-dimensional: the flux needs d/dxi_d of the velocity
+// only, and with beta = 1/2 the common solution of a face is its minus side's
+// and the common viscous flux its plus side's.  So with u^I(-) the minus
+// neighbour's plus trace and u^I(+) the line's own plus trace, the corrected
+// derivative g = Dt u + g_L u^I(-) + g_R u^I(+) is known from the line and one
+// neighbour trace, and the viscous flux at the plus neighbour's minus face from
+// that neighbour's line and the own plus trace (its own plus trace is its
+// u^I(+)).  Neither the gradient nor a face array goes through memory.
+//
+// A workgroup takes a brick of E elements into LDS (straight from memory), one
+// lane per element line and direction; the neighbours' lines come from the tile
+// or from memory.  The four line derivatives of the three directions are summed
+// in the order x, y, z over the tile, which is then R.
+//
+// Floor: 8 values per point (0.22 ms at the rate of a copy for p = 4 on 51^3
+// hexes, 16.6 M points): 0.50 ms there, with 148 VGPRs, 12 waves per CU and the 24
+// neighbour values per point out of the caches; the four kernels above, 66 values
+// per point through memory, take 3.3 ms.
+// ---------------------------------------------------------------------------
+template <int P> struct AcmLineShape {
+    static constexpr int M = P + 1, E = 64 / (M * M);
+    static constexpr int WPE = P >= 5 ? 3 : 1;   // 168 VGPRs, three waves per SIMD
+};
+
+// Operators of one order in LDS: Dt, g_L, g_R, l(-1), l(+1), and for the end
+// slope of a line am[l] = sum_r l_r(-1) Dt[r][l], bl = sum_r l_r(-1) g_L[r],
+// br = sum_r l_r(-1) g_R[r].
+template <int M> struct AcmOps {
+    static constexpr int Dt = 0, gl = M * M, gr = gl + M, lm = gr + M, lp = lm + M, am = lp + M, bl = am + M,
+                         br = bl + 1, size = br + 1, room = (size + 1) / 2 * 2;
+};
+
+template <int M>
+__device__ __forceinline__ double dot(const double *__restrict__ w, const double (&x)[M])
+{
+    double s = 0.0;
+#pragma unroll
+    for (int l = 0; l < M; ++l) s = fma(w[l], x[l], s);
+    return s;
+}
+
+// Common flux through a face of direction D between L (minus side) and R, with
+// the common viscous flux fv, times the face scaling nmag.
+template <int D>
+__device__ __forceinline__ void acm_face(const double (&L)[NA], const double (&R)[NA],
+                                         const double (&fv)[3], const AcmArgs &A, double (&out)[NA])
+{
+    const double vL = L[1 + D], vR = R[1 + D], n = A.nmag[D];
+    const double lam = fmax(fabs(vL) + sqrt(fma(vL, vL, A.zeta)), fabs(vR) + sqrt(fma(vR, vR, A.zeta)));
+    out[0] = n * (0.5 * A.zeta * (vL + vR) - 0.5 * lam * (R[0] - L[0]));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double mL = L[1 + c] * vL, mR = R[1 + c] * vR;
+        if (c == D) mL += L[0], mR += R[0];
+        out[1 + c] = n * (0.5 * (mL + mR) - 0.5 * lam * (R[1 + c] - L[1 + c]) + fv[c] +
+                          A.tau * (L[1 + c] - R[1 + c]));
+    }
+}
+
+// What a line needs of its neighbours: the minus neighbour's plus trace (nm), the
+// plus neighbour's minus trace (np), and for the velocities the part of the plus
+// neighbour's end slope that its own line gives (sp = am . u) and its plus trace
+// (pp).
+struct AcmNbr {
+    double nm[NA], np[NA], sp[3], pp[3];
+};
+template <int M>
+__device__ __forceinline__ void acm_minus(AcmNbr &b, const double (&x)[NA][M], const double *__restrict__ ops)
+{
+#pragma unroll
+    for (int v = 0; v < NA; ++v) b.nm[v] = dot<M>(ops + AcmOps<M>::lp, x[v]);
+}
+template <int M>
+__device__ __forceinline__ void acm_plus(AcmNbr &b, const double (&x)[NA][M], const double *__restrict__ ops)
+{
+#pragma unroll
+    for (int v = 0; v < NA; ++v) b.np[v] = dot<M>(ops + AcmOps<M>::lm, x[v]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        b.sp[c] = dot<M>(ops + AcmOps<M>::am, x[1 + c]);
+        b.pp[c] = dot<M>(ops + AcmOps<M>::lp, x[1 + c]);
+    }
+}
+
+template <int P, int D>
+__device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const double *__restrict__ sop,
+                                         const AcmNbr &nb, int L, const AcmArgs &A, double (&div)[NA][P + 1])
+{
+    constexpr int M = P + 1, NS = M * M * M, STR = D == 0 ? 1 : (D == 1 ? M : M * M);
+    using OL = AcmOps<M>;
+    const double *Ue = Ut + lt_base<P, double, D>(L);
+    const double ndd = A.nvec[4 * D], nuJ = A.nu * A.Jinv[4 * D];
+    const double bl = sop[OL::bl], br = sop[OL::br];
+    double FIm[NA], FIp[NA], up[NA], X[NA][M];
+    const double (&nm)[NA] = nb.nm;
+    {
+        double um[NA], fm[3], fp[3];
+#pragma unroll
+        for (int v = 0; v < NA; ++v) {
+            line_load<M, STR>(Ue + v * NS, X[v]);
+            um[v] = dot<M>(sop + OL::lm, X[v]);
+            up[v] = dot<M>(sop + OL::lp, X[v]);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            // the plus sides' slopes at their minus faces: the own one, the plus neighbour's
+            fm[c] = -nuJ * fma(br, up[1 + c], fma(bl, nm[1 + c], dot<M>(sop + OL::am, X[1 + c])));
+            fp[c] = -nuJ * fma(br, nb.pp[c], fma(bl, up[1 + c], nb.sp[c]));
+        }
+        acm_face<D>(nm, um, fm, A, FIm);
+        acm_face<D>(up, nb.np, fp, A, FIp);
+#pragma unroll
+        for (int v = 0; v < NA; ++v) __asm__ volatile("" : "+v"(FIm[v]), "+v"(FIp[v]), "+v"(up[v]));
+    }
+    // the transformed fluxes of the velocities at the points, row by row with
+    // the corrected derivative they contain
+    double F[3][M];
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+        __builtin_amdgcn_sched_barrier(0);   // one row's operator values at a time
+        const double glr = sop[OL::gl + r], grr = sop[OL::gr + r];
+        double Dr[M];
+#pragma unroll
+        for (int l = 0; l < M; ++l) Dr[l] = sop[OL::Dt + r * M + l];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double g = fma(glr, nm[1 + c], fma(grr, up[1 + c], dot<M>(Dr, X[1 + c])));
+            double f = fma(X[1 + c][r], X[1 + D][r], -nuJ * g);
+            if (c == D) f += X[0][r];
+            F[c][r] = ndd * f;
+            // formed here, or the compiler sinks every row to the next loop and
+            // holds the whole operator in registers (222 against 140 VGPRs at p = 4)
+            __asm__ volatile("" : "+v"(F[c][r]));
+        }
+    }
+    const double zn = A.zeta * ndd;
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+        __builtin_amdgcn_sched_barrier(0);
+        const double glr = sop[OL::gl + r], grr = sop[OL::gr + r];
+        double Dr[M];
+#pragma unroll
+        for (int l = 0; l < M; ++l) Dr[l] = sop[OL::Dt + r * M + l];
+        div[0][r] = fma(glr, FIm[0], fma(grr, FIp[0], zn * dot<M>(Dr, X[1 + D])));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) div[1 + c][r] = fma(glr, FIm[1 + c], fma(grr, FIp[1 + c], dot<M>(Dr, F[c])));
+#pragma unroll
+        for (int v = 0; v < NA; ++v) __asm__ volatile("" : "+v"(div[v][r]));
+    }
+}
+
+template <int P>
+__global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(AcmLineShape<P>::WPE, 8)))
+    k_acm_lines(const double *__restrict__ U, double *__restrict__ R, const double *__restrict__ ops,
+                AcmArgs A, Bricks g)
+{
+    constexpr int M = P + 1, NS = M * M * M, NF = M * M, E = AcmLineShape<P>::E;
+    using LT = LinesTile<P, double, NA>;
+    using OL = AcmOps<M>;
+    constexpr int RAW = LT::RAW, UNITS = (LT::CH + 63) / 64;
+    static_assert(!LT::ODD, "an element is a whole number of 16-byte chunks");
+    __shared__ __align__(16) double sop[OL::room];
+    __shared__ __align__(16) double sU[E * LT::SLOT];
+    const int brick = brick_of(g, blockIdx.x);
+    if (brick < 0) return;
+    const int row = g.by_gx(brick), lay = g.by_gy(row);
+    const int cx = (brick - row * g.gx) * g.bx, cy = (row - lay * g.gy) * g.by, cz = lay * g.bz;
+    const int d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double opv = 0.0;
+    if (threadIdx.x < OL::size) opv = ops[threadIdx.x];
+    for (int u = d; u < E * UNITS; u += 3) {
+        const int s = u / UNITS, e = brick_slot(g, s, cx, cy, cz, A.nx, A.ny, A.nz).e;
+        if (e >= 0) slot_load<LT>(U + (int64_t)e * RAW, 0, sU + s * LT::SLOT, u - s * UNITS);
+    }
+    const int lane = threadIdx.x & 63, el = lane / NF, L = lane - el * NF;
+    const BrickSlot me = brick_slot(g, el, cx, cy, cz, A.nx, A.ny, A.nz);
+    const bool act = el < E && me.e >= 0;
+    // the neighbours' lines: from memory for a neighbour outside the brick, from
+    // the tile once it is loaded otherwise
+    AcmNbr nb;
+    const int sd = d == 0 ? me.sx : (d == 1 ? me.sy : me.sz);
+    const int bd = d == 0 ? g.bx : (d == 1 ? g.by : g.bz);
+    const int x = sd + (d == 0 ? cx : (d == 1 ? cy : cz));
+    const int n = d == 0 ? A.nx : (d == 1 ? A.ny : A.nz);
+    const bool inm = act && sd > 0, inp = act && sd + 1 < bd && x + 1 < n;
+    auto lines = [&](const double *Un, auto dc, double (&o)[NA][M]) {
+        constexpr int D = decltype(dc)::value, STR = D == 0 ? 1 : (D == 1 ? M : M * M);
+        const double *p = Un + lt_base<P, double, D>(L);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < NA; ++v)
+#pragma unroll
+            for (int l = 0; l < M; ++l) o[v][l] = p[v * NS + l * STR];
+    };
+    auto from_memory = [&](auto dc) {
+        const int le = d == 0 ? 1 : (d == 1 ? A.nx : A.nx * A.ny);
+        const double *Um = U + (int64_t)(me.e + (x == 0 ? n - 1 : -1) * le) * RAW;
+        const double *Up = U + (int64_t)(me.e + (x + 1 == n ? 1 - n : 1) * le) * RAW;
+        double o[NA][M];
+        if (act && !inm && !inp) {
+            double q[NA][M];
+            lines(Um, dc, o);
+            lines(Up, dc, q);
+            acm_minus<M>(nb, o, ops);
+            acm_plus<M>(nb, q, ops);
+        } else if (act && !inm) {
+            lines(Um, dc, o);
+            acm_minus<M>(nb, o, ops);
+        } else if (act && !inp) {
+            lines(Up, dc, o);
+            acm_plus<M>(nb, o, ops);
+        }
+    };
+    if (d == 0) from_memory(Dir<0>{});
+    else if (d == 1) from_memory(Dir<1>{});
+    else from_memory(Dir<2>{});
+    if (threadIdx.x < OL::size) sop[threadIdx.x] = opv;
+    // the direct loads into LDS have arrived (their count is not tracked by the
+    // barrier)
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    double *Ut = sU + (act ? el : 0) * LT::SLOT;
+    const int ls = (d == 0 ? 1 : (d == 1 ? g.bx : g.bx * g.by)) * LT::SLOT;
+    double div[NA][M];
+    auto task = [&](auto dc) {
+        constexpr int D = decltype(dc)::value;
+        double o[NA][M];
+        if (inm) {
+            lines(Ut - ls, dc, o);
+            acm_minus<M>(nb, o, sop);
+        }
+        if (inp) {
+            lines(Ut + ls, dc, o);
+            acm_plus<M>(nb, o, sop);
+        }
+        if (act) acm_line<P, D>(Ut, sop, nb, L, A, div);
+    };
+    if (d == 0) task(Dir<0>{});
+    else if (d == 1) task(Dir<1>{});
+    else task(Dir<2>{});
+    // every lane has read the tile: the sums of the directions replace it
+    auto add = [&](auto dc) {
+        constexpr int D = decltype(dc)::value, STR = D == 0 ? 1 : (D == 1 ? M : M * M);
+        double *Ue = Ut + lt_base<P, double, D>(L);
+#pragma unroll
+        for (int v = 0; v < NA; ++v) {
+            double o[M];
+            if constexpr (D == 0) {
+#pragma unroll
+                for (int r = 0; r < M; ++r) o[r] = div[v][r];
+            } else {
+                line_load<M, STR>(Ue + v * NS, o);
+#pragma unroll
+                for (int r = 0; r < M; ++r) o[r] = D == 2 ? -A.inv_det * (o[r] + div[v][r]) : o[r] + div[v][r];
+            }
+            line_put<M, STR>(Ue + v * NS, o);
+        }
+    };
+    __syncthreads();
+    if (act && d == 0) add(Dir<0>{});
+    __syncthreads();
+    if (act && d == 1) add(Dir<1>{});
+    __syncthreads();
+    if (act && d == 2) add(Dir<2>{});
+    __syncthreads();
+    for (int u = d; u < E * UNITS; u += 3) {
+        const int s = u / UNITS, e = brick_slot(g, s, cx, cy, cz, A.nx, A.ny, A.nz).e;
+        if (e >= 0) slot_store<LT>(sU + s * LT::SLOT, 0, R + (int64_t)e * RAW, u - s * UNITS);
+    }
+}
+
 // Dual time stepping of this system (Sec. 5): dU/dtau = R*(U) with the BDF
 // source on the velocity only, dU/dt = a U + B (BDF2: a = 3/(2 dt),
 // B = (-4 Un + Unm1)/(2 dt); BDF1: a = 1/dt, B = -Un/dt), classical RK4
@@ -346,6 +629,7 @@ struct fr_acm {
     fr_plan *plan = nullptr;
     fr::AcmArgs args;
     double *utr = nullptr, *Q = nullptr, *FI = nullptr;
+    double *ops = nullptr;   // operators of k_acm_lines
     // dual time stepping (allocated on its first call): residual, stage state,
     // RK accumulator, BDF constant, norm partials and result, pinned read-back
     double *R = nullptr, *S = nullptr, *acc = nullptr, *B = nullptr, *part = nullptr;
@@ -411,8 +695,29 @@ int launch_front(fr_acm *a, const double *U, hipStream_t s)
 #undef FR_ACM_GRAD
 }
 
+// k_acm_lines takes diagonal Jacobians, the switch at beta = 1/2 (where the
+// viscous flux of a face needs the nearest neighbours only) and states whose
+// elements start on 16-byte boundaries; everything else runs the four kernels.
+bool lines_take(const fr_acm *a, const double *U, const double *R)
+{
+    return a->args.diag && a->args.beta == 0.5 && (((uintptr_t)U | (uintptr_t)R) & 15) == 0;
+}
+
+template <int M>
+int launch_lines(fr_acm *a, const double *U, double *R, hipStream_t s)
+{
+    const Bricks g = bricks_for(AcmLineShape<M - 1>::E, 8, a->args.nx, a->args.ny, a->args.nz);
+    hipLaunchKernelGGL(k_acm_lines<M - 1>, dim3((g.nb + 7) / 8 * 8), dim3(192), 0, s, U, R, a->ops, a->args, g);
+    return check_hip(hipGetLastError(), "k_acm_lines launch");
+}
+
 int launch_residual(fr_acm *a, const double *U, double *R, hipStream_t s)
 {
+    if (lines_take(a, U, R)) {
+#define FR_ACM_LINES(M) launch_lines<M>(a, U, R, s)
+        FR_ACM_ORDERS(FR_ACM_LINES)
+#undef FR_ACM_LINES
+    }
     const int64_t ne = a->plan->ne;
     const int ns = a->args.m * a->args.m * a->args.m;
     if (int rc = launch_front(a, U, s)) return rc;
@@ -497,6 +802,7 @@ fr_acm *fr_acm_create(fr_plan *plan, double ldg_beta, double ldg_tau)
             A.nhat[3 * d + j] = plan->c64.nhat[d][j];
         }
     }
+    A.diag = plan->c64.diag;
     A.inv_det = 1.0 / plan->detJ;
     A.zeta = plan->zeta;
     A.nu = plan->nu;
@@ -507,6 +813,27 @@ fr_acm *fr_acm_create(fr_plan *plan, double ldg_beta, double ldg_tau)
     if (check_hip(hipMalloc((void **)&a->utr, (size_t)ne * 6 * NA * nfp * sizeof(double)), "hipMalloc(acm traces)") ||
         check_hip(hipMalloc((void **)&a->Q, (size_t)ne * 9 * ns * sizeof(double)), "hipMalloc(acm gradient)") ||
         check_hip(hipMalloc((void **)&a->FI, (size_t)ne * 3 * NA * nfp * sizeof(double)), "hipMalloc(acm fluxes)")) {
+        fr_acm_destroy(a);
+        return nullptr;
+    }
+    // Dt, g_L, g_R, l(-1), l(+1), then l(-1) applied to Dt, g_L and g_R
+    double h[LINE_OPS], *o = h;
+    for (int i = 0; i < m * m; ++i) *o++ = A.Dt[i];
+    for (const double *v : {A.gl, A.gr, A.lm, A.lp})
+        for (int i = 0; i < m; ++i) *o++ = v[i];
+    for (int l = 0; l < m; ++l) {
+        double am = 0.0;
+        for (int r = 0; r < m; ++r) am += A.lm[r] * A.Dt[r * m + l];
+        *o++ = am;
+    }
+    for (const double *v : {A.gl, A.gr}) {
+        double b = 0.0;
+        for (int r = 0; r < m; ++r) b += A.lm[r] * v[r];
+        *o++ = b;
+    }
+    if (check_hip(hipMalloc((void **)&a->ops, sizeof h), "hipMalloc(acm operators)") ||
+        check_hip(hipMemcpy(a->ops, h, (size_t)(o - h) * sizeof(double), hipMemcpyHostToDevice),
+                  "hipMemcpy(acm operators)")) {
         fr_acm_destroy(a);
         return nullptr;
     }
@@ -581,6 +908,7 @@ void fr_acm_destroy(fr_acm *a)
     if (a->utr) (void)hipFree(a->utr);
     if (a->Q) (void)hipFree(a->Q);
     if (a->FI) (void)hipFree(a->FI);
+    if (a->ops) (void)hipFree(a->ops);
     double *bufs[5] = {a->R, a->S, a->acc, a->B, a->part};
     for (double *b : bufs)
         if (b) (void)hipFree(b);

@@ -1,0 +1,240 @@
+// Bricks of elements, their LDS tiles and their lines: what the kernels that
+// take an element's lines one per lane share.
+#pragma once
+
+#include <algorithm>
+
+#include "fr_device.h"
+
+namespace fr {
+namespace dev {
+
+// The m values of one line (first value p, stride STR) into registers; an
+// x-line (STR = 1) is contiguous and is read in 16- or 8-byte vectors where
+// its length and the element size keep them aligned.
+template <int M, int STR, typename T>
+__device__ __forceinline__ void line_load(const T *__restrict__ p, T (&x)[M])
+{
+    if constexpr (STR == 1 && (M * sizeof(T)) % 16 == 0) {
+        using V = typename V16<T>::type;
+        constexpr int W = 16 / sizeof(T);
+#pragma unroll
+        for (int k = 0; k < M / W; ++k) {
+            const V v = reinterpret_cast<const V *>(p)[k];
+#pragma unroll
+            for (int w = 0; w < W; ++w) x[k * W + w] = v[w];
+        }
+    } else if constexpr (STR == 1 && sizeof(T) == 4 && M % 2 == 0) {
+        typedef float f2v __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int k = 0; k < M / 2; ++k) {
+            const f2v v = reinterpret_cast<const f2v *>(p)[k];
+            x[2 * k] = v[0];
+            x[2 * k + 1] = v[1];
+        }
+    } else {
+#pragma unroll
+        for (int l = 0; l < M; ++l) x[l] = p[l * STR];
+    }
+}
+
+// The m values of one line into LDS (the layout of line_load).
+template <int M, int STR, typename T>
+__device__ __forceinline__ void line_put(T *__restrict__ p, const T (&x)[M])
+{
+    if constexpr (STR == 1 && (M * sizeof(T)) % 16 == 0) {
+        using V = typename V16<T>::type;
+        constexpr int W = 16 / sizeof(T);
+#pragma unroll
+        for (int k = 0; k < M / W; ++k) {
+            V v;
+#pragma unroll
+            for (int w = 0; w < W; ++w) v[w] = x[k * W + w];
+            reinterpret_cast<V *>(p)[k] = v;
+        }
+    } else {
+#pragma unroll
+        for (int l = 0; l < M; ++l) p[l * STR] = x[l];
+    }
+}
+
+// First point of the direction-D line through face point L.
+template <int P, typename T, int D>
+__device__ __forceinline__ int lt_base(int L)
+{
+    constexpr int M = P + 1;
+    const int a = L % M, b = L / M;
+    return D == 0 ? M * L : (D == 1 ? a + M * M * b : L);
+}
+
+// Bricks of elements for the line forms.  A workgroup takes bx * by * bz
+// elements (at most LinesShape::E), neighbours of each other in the lattice, so
+// that the faces between them are formed from the tile; bricks at the lattice's
+// upper ends may stick out of it (those slots idle).
+//
+// Division of n < 2^31 by a number fixed on the host: n / d = n m >> s with
+// 2^(s - 32) < d <= 2^(s - 31), m = ceil(2^s / d) (the excess of m d over 2^s is
+// below 2^(s - 31), too little to reach the next quotient).
+struct FastDiv {
+    uint32_t m;
+    int s;
+    __device__ __forceinline__ unsigned operator()(unsigned n) const
+    {
+        return (unsigned)(((uint64_t)n * m) >> s);
+    }
+};
+struct Bricks {
+    int bx, by, bz;        // elements of a brick along x, y, z
+    int mx, mxy;           // ceil(2^16 / bx), ceil(2^16 / (bx by)): n / bx = n mx >> 16 for n < 256
+    int gx, gy;            // bricks of the lattice along x, y
+    FastDiv by_gx, by_gy;
+    unsigned nb;           // bricks of the lattice
+    unsigned chunk;        // bricks of an XCD's share of a group (brick_of)
+    FastDiv by_group;      // by 8 chunk
+};
+
+// Elements of the brick (slot coordinates sx, sy, sz, lattice element e; e < 0:
+// slot not in use).
+struct BrickSlot {
+    int sx, sy, sz, e;
+};
+__device__ __forceinline__ BrickSlot brick_slot(const Bricks &g, int s, int cx, int cy, int cz,
+                                                int nx, int ny, int nz)
+{
+    BrickSlot r;
+    r.sz = (s * g.mxy) >> 16;
+    const int q = s - r.sz * (g.bx * g.by);
+    r.sy = (q * g.mx) >> 16;
+    r.sx = q - r.sy * g.bx;
+    const int x = cx + r.sx, y = cy + r.sy, z = cz + r.sz;
+    r.e = r.sz < g.bz && x < nx && y < ny && z < nz ? x + nx * (y + ny * z) : -1;
+    return r;
+}
+
+// Workgroup b's brick, or -1.  Consecutive workgroups go to the eight XCDs in
+// turn, each with an L2 of its own.  A group of 8 g.chunk bricks (one layer of
+// the lattice along z) is dealt out so that every XCD works on a contiguous
+// eighth of it: y neighbours then share an L2, and all XCDs stay on one compact
+// front of the lattice, whose last layer the memory-side cache still holds when
+// the next one reads its z neighbours.
+__device__ __forceinline__ int brick_of(const Bricks &g, unsigned b)
+{
+    const unsigned first = g.by_group(b) * 8 * g.chunk, r = b - first;
+    if (first >= g.nb) return -1;
+    const unsigned share = min(g.chunk, (g.nb - first + 7) / 8);
+    const unsigned i = r >> 3, k = r & 7;
+    const unsigned brick = first + k * share + i;
+    return i < share && brick < g.nb ? (int)brick : -1;
+}
+
+// LDS tile of the line forms: one slot per element, 16-byte aligned.  The
+// element's block starts in its slot at the same offset from a 16-byte
+// boundary as in global memory (where an odd element may start 8 bytes, in
+// single precision 4, 8 or 12, after one), so both sides move whole aligned
+// 16-byte chunks.
+template <int P, typename T, int NVAR = NV>
+struct LinesTile {
+    static constexpr int M = P + 1, RAW = NVAR * M * M * M, VW = 16 / sizeof(T);
+    static constexpr bool ODD = RAW % VW != 0;
+    static constexpr int CH = (RAW + (ODD ? VW - 1 : 0) + VW - 1) / VW;   // chunks of a slot
+    static constexpr int SLOT = CH * VW;
+    static constexpr int OPS = LinesLds<P, T>::OPS;   // the operator block in front of the tile
+    __device__ __forceinline__ static int off(int slot, int e)
+    {
+        return slot * SLOT + (ODD ? (int)(((unsigned)e * (unsigned)RAW) % VW) : 0);
+    }
+};
+
+// One element's block into its slot by direct loads into LDS: every wave takes
+// 64 chunks of 16 bytes at a time and waits for none of them (the caller waits
+// for vmcnt before the barrier).  lo is the block's offset in its slot; bytes
+// before the block in its first chunk belong to the previous element (lo > 0
+// only for e > 0), and the chunk that holds the block's end is read in
+// four-byte words up to it, so nothing past the state is touched.
+template <typename LT, typename T>
+__device__ __forceinline__ void slot_load(const T *__restrict__ src, int lo, T *slot, int unit)
+{
+    typedef __attribute__((address_space(1))) const void gptr;
+    typedef __attribute__((address_space(3))) void lptr;
+    const int lane = threadIdx.x & 63;
+    const int whole = (lo + LT::RAW) / LT::VW;      // chunks without the block's last, partial one
+    const T *s0 = src - lo;
+    const int c0 = unit * 64;
+    if (c0 + lane < whole)
+        __builtin_amdgcn_global_load_lds((gptr *)(s0 + (c0 + lane) * LT::VW), (lptr *)(slot + c0 * LT::VW), 16,
+                                         0, 0);
+    if constexpr (LT::ODD) {
+        const int words = ((lo + LT::RAW) % LT::VW) * (int)(sizeof(T) / 4);
+        if (unit == (LT::CH - 1) / 64 && lane < words)
+            __builtin_amdgcn_global_load_lds((gptr *)((const int *)(s0 + whole * LT::VW) + lane),
+                                             (lptr *)(slot + whole * LT::VW), 4, 0, 0);
+    }
+}
+
+// The reverse: 64 chunks of an element's slot to its block in memory.
+template <typename LT, typename T>
+__device__ __forceinline__ void slot_store(const T *slot, int lo, T *__restrict__ dst, int unit)
+{
+    using V = typename V16<T>::type;
+    const int c = unit * 64 + (threadIdx.x & 63);
+    if (c >= LT::CH) return;
+    const int v0 = c * LT::VW - lo;                 // first value of the chunk
+    if (!LT::ODD || (v0 >= 0 && v0 + LT::VW <= LT::RAW)) {
+        __builtin_nontemporal_store(reinterpret_cast<const V *>(slot)[c], reinterpret_cast<V *>(dst - lo) + c);
+    } else {
+#pragma unroll
+        for (int w = 0; w < LT::VW; ++w)
+            if (v0 + w >= 0 && v0 + w < LT::RAW) __builtin_nontemporal_store(slot[c * LT::VW + w], dst + v0 + w);
+    }
+}
+
+}  // namespace dev
+
+// The bricks a lattice is cut into for a kernel whose workgroups hold at most E
+// elements: the shape with the least cost, bricks (4 E + pairs of outer faces)
+// (a brick costs its workgroup's time whether its slots are in use or not, and
+// the neighbours' traces on its outer faces come from memory; at p = 1 on 128^3
+// hexes 4x4x1 takes 0.88 ms and 16x1x1 0.93 in double, 0.52 and 0.60 in single
+// precision), the longest along x where it is equal (at p = 4 on 51^3 hexes 2x1x1
+// takes 0.98 ms and 1x2x1 1.02).  A lattice of up to 256 elements (one
+// for each CU; 512 in single precision, whose bricks are half as large) gets
+// one-element bricks and one of up to E times that smaller ones in proportion:
+// such a call takes one workgroup's latency, which grows with its brick (RK4 step
+// at p = 3 in double on 6^3 hexes: 44 us with one-element bricks, 56 with four).
+inline dev::FastDiv fast_div(uint32_t d)
+{
+    dev::FastDiv f{0, 31};
+    while (f.s < 62 && (uint64_t)1 << (f.s - 31) < d) ++f.s;
+    f.m = (uint32_t)((((uint64_t)1 << f.s) + d - 1) / d);
+    return f;
+}
+
+inline dev::Bricks bricks_for(int E, int esize, int nx, int ny, int nz)
+{
+    const int64_t ne = (int64_t)nx * ny * nz;
+    const int few = esize == 8 ? 256 : 512;
+    const int most = (int)std::min<int64_t>(E, (ne + few - 1) / few);
+    dev::Bricks g{};
+    double best = 0.0;
+    for (int bx = most; bx >= 1; --bx)
+        for (int by = 1; bx * by <= most; ++by)
+            for (int bz = 1; bx * by * bz <= most; ++bz) {
+                const double nb = (double)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
+                const double cost = nb * (4 * E + bx * by + by * bz + bz * bx);
+                if (g.bx && cost >= best) continue;
+                best = cost;
+                g.bx = bx, g.by = by, g.bz = bz;
+            }
+    g.mx = (65536 + g.bx - 1) / g.bx;
+    g.mxy = (65536 + g.bx * g.by - 1) / (g.bx * g.by);
+    g.gx = (nx + g.bx - 1) / g.bx;
+    g.gy = (ny + g.by - 1) / g.by;
+    g.nb = (unsigned)g.gx * (unsigned)g.gy * (unsigned)((nz + g.bz - 1) / g.bz);
+    g.chunk = (unsigned)(((int64_t)g.gx * g.gy + 7) / 8);
+    g.by_gx = fast_div(g.gx);
+    g.by_gy = fast_div(g.gy);
+    g.by_group = fast_div(8 * g.chunk);
+    return g;
+}
+
+}  // namespace fr
