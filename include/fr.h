@@ -351,9 +351,9 @@ void fr_acm_destroy(fr_acm *a);
  * plan's lattice connectivity (neighbours along +-xi_d, periodic) and must be
  * conforming: the plus face of an element and the minus face of its
  * neighbour are the same quadrilateral (a periodic shift of it is allowed:
- * only tangents enter).  The common flux on a face is evaluated once, with
- * the minus-side element's metric.  det J must be positive at every solution
- * point (not checked).  With affine corners the result is fr_residual's.
+ * only tangents enter).  The common flux on a face takes the metric from the
+ * corners of either element (equal to rounding on a conforming face).  det J
+ * must be positive at every solution point (not checked).  With affine corners the result is fr_residual's.
  *
  * fr_lhex_create -- bind to the plan (borrowed; its order, lattice, zeta, nu
  * and T are used, its Jacobian, precision and variant are not) and allocate

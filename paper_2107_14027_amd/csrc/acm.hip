@@ -49,8 +49,6 @@ struct AcmArgs {
 // The operators k_acm_lines takes (AcmOps<m>).
 constexpr int LINE_OPS = MM * MM + 5 * MM + 2;
 
-template <int D> struct Dir { static constexpr int value = D; };
-
 __device__ __forceinline__ int line_pt(int m, int d, int a, int b, int l)
 {
     return d == 0 ? l + m * (a + m * b) : (d == 1 ? a + m * (l + m * b) : a + m * (b + m * l));
@@ -377,7 +375,7 @@ __device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const do
         acm_face<D>(nm, um, fm, A, FIm);
         acm_face<D>(up, nb.np, fp, A, FIp);
 #pragma unroll
-        for (int v = 0; v < NA; ++v) __asm__ volatile("" : "+v"(FIm[v]), "+v"(FIp[v]), "+v"(up[v]));
+        for (int v = 0; v < NA; ++v) pin(FIm[v]), pin(FIp[v]), pin(up[v]);
     }
     // the transformed fluxes of the velocities at the points, row by row with
     // the corrected derivative they contain
@@ -397,7 +395,7 @@ __device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const do
             F[c][r] = ndd * f;
             // formed here, or the compiler sinks every row to the next loop and
             // holds the whole operator in registers (222 against 140 VGPRs at p = 4)
-            __asm__ volatile("" : "+v"(F[c][r]));
+            pin(F[c][r]);
         }
     }
     const double zn = A.zeta * ndd;
@@ -412,7 +410,7 @@ __device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const do
 #pragma unroll
         for (int c = 0; c < 3; ++c) div[1 + c][r] = fma(glr, FIm[1 + c], fma(grr, FIp[1 + c], dot<M>(Dr, F[c])));
 #pragma unroll
-        for (int v = 0; v < NA; ++v) __asm__ volatile("" : "+v"(div[v][r]));
+        for (int v = 0; v < NA; ++v) pin(div[v][r]);
     }
 }
 

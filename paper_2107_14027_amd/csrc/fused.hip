@@ -384,42 +384,6 @@ __device__ __forceinline__ void neighbour_table(int *sNb, int e0, int nel, int n
     }
 }
 
-// Common normal flux through a face of direction d, evaluated by the element
-// on one side: own = its trace, oth = the neighbour's, own_minus = the element
-// is on the minus side of the face (its + face).  Equal, bit for bit, to the
-// same flux evaluated by the neighbour, because every asymmetric term is
-// written as a signed difference oth - own whose sign is carried by an exact
-// sign flip of lambda, and every symmetric term is a commutative sum.
-//   out[0]     Rusanov dissipation on P, -|n| lambda (P_plus - P_minus) / 2
-//   out[1..3]  momentum common flux (times |n_d|)
-//   out[4..6]  mean velocity
-template <typename T>
-__device__ __forceinline__ void common_flux_sided(const T own[NTR], const T oth[NTR], bool own_minus,
-                                                  const T nh[3], T nmag, T zeta, T nu, T out[NTR])
-{
-    T vo = own[1] * nh[0];
-    vo = fma(own[2], nh[1], vo);
-    vo = fma(own[3], nh[2], vo);
-    T vt = oth[1] * nh[0];
-    vt = fma(oth[2], nh[1], vt);
-    vt = fma(oth[3], nh[2], vt);
-    // lambda = max over both sides of |v| + sqrt(v^2 + zeta), evaluated once
-    // at the larger |v| (the expression is monotone in |v| after rounding too)
-    const T vm = fmax(fabs(vo), fabs(vt));
-    const T lam = vm + sqrt(fma(vm, vm, zeta));
-    const T hm = T(0.5) * nmag;
-    // P_plus - P_minus = (own_minus ? 1 : -1) (P_oth - P_own)
-    const T slam = own_minus ? lam : -lam;
-    out[0] = (-hm * slam) * (oth[0] - own[0]);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const T fo = fma(own[1 + i], vo, fma(own[0], nh[i], -nu * own[4 + i]));
-        const T ft = fma(oth[1 + i], vt, fma(oth[0], nh[i], -nu * oth[4 + i]));
-        out[1 + i] = hm * fma(oth[1 + i] - own[1 + i], -slam, fo + ft);
-        out[4 + i] = T(0.5) * (own[1 + i] + oth[1 + i]);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // k_trace: per batch of consecutive elements staged in LDS, every face value
 // an element's neighbours need, written to the neighbour's receiving block.
@@ -494,7 +458,6 @@ __global__ void __launch_bounds__((TraceShape<P, T>::NT))
 // k_fused
 // LDS: sU[EMAX][13][NS] | sF[EMAX][9][NS] | sFI[6][EMAX][CHP] | ops | geometry
 // ---------------------------------------------------------------------------
-template <int D> struct Dir { static constexpr int value = D; };
 
 // Divergence as line tasks (diagonal Jacobian, p = 6, where it measured faster
 // than the point-wise form; slower from p = 4 down): one thread per

@@ -18,9 +18,13 @@
 //                                                      utr[e][6][7][m^2]
 //   k_lh_common  corners, utr -> |S| F^I               FI[e][3][13][m^2]  (plus faces)
 //   k_lh_resid   corners, U, FI -> R
+// They run for states that are only 8-byte aligned.  States on 16-byte boundaries
+// (every allocation of the library or of torch) take one kernel, k_lh_lines, in
+// which each side of a face evaluates its common flux with its own corners' metric
+// (equal to rounding where the corners of the two elements are the same points).
 #include <cmath>
 
-#include "fr_device.h"
+#include "metric_lines.h"
 
 namespace fr {
 namespace {
@@ -248,6 +252,81 @@ __global__ void __launch_bounds__(RES_TB) k_lh_resid(const double *__restrict__ 
     }
 }
 
+// The trilinear map's metric along the line of direction d through face point
+// (a, b), from the element's corners.  The corners are taken with the line's
+// direction first and the other two in cyclic order behind it, so one formula
+// serves the three directions; their monomial coefficients come from sums and
+// differences over one bit after the other, without the factor 1/8, which is
+// put in last.
+__device__ __forceinline__ dev::TrilinearGeo line_metric(const double *__restrict__ Ce, int d, double xa, double xb)
+{
+    const int c1 = d == 2 ? 1 : 2 << d, c2 = d == 0 ? 4 : (d == 1 ? 1 : 2);   // corner bits of d + 1 and d + 2
+    const double xe = d == 1 ? xb : xa, xf = d == 1 ? xa : xb;               // coordinates along them
+    double b[8][3];   // 1, x, e, x e, f, x f, e f, x e f
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            b[c][j] = Ce[3 * ((c & 1 ? 1 << d : 0) + (c & 2 ? c1 : 0) + (c & 4 ? c2 : 0)) + j];
+#pragma unroll
+    for (int bit = 1; bit < 8; bit *= 2)
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            if (!(c & bit))
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    const double lo = b[c][j], hi = b[c | bit][j];
+                    b[c][j] = hi + lo;
+                    b[c | bit][j] = hi - lo;
+                }
+    dev::TrilinearGeo g;
+    double a0[3], p0[3], p1[3], q0[3], q1[3];   // a_d, a_{d+1} = p0 + p1 xi, a_{d+2} = q0 + q1 xi, times 8
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        a0[j] = fma(xf, fma(b[7][j], xe, b[5][j]), fma(b[3][j], xe, b[1][j]));
+        p0[j] = fma(b[6][j], xf, b[2][j]), p1[j] = fma(b[7][j], xf, b[3][j]);
+        q0[j] = fma(b[6][j], xe, b[4][j]), q1[j] = fma(b[7][j], xe, b[5][j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int u = (j + 1) % 3, v = (j + 2) % 3;
+        g.s[j][0] = (p0[u] * q0[v] - p0[v] * q0[u]) * (1.0 / 64);
+        g.s[j][1] = ((p0[u] * q1[v] - p0[v] * q1[u]) + (p1[u] * q0[v] - p1[v] * q0[u])) * (1.0 / 64);
+        g.s[j][2] = (p1[u] * q1[v] - p1[v] * q1[u]) * (1.0 / 64);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) g.d[i] = (a0[0] * g.s[0][i] + a0[1] * g.s[1][i] + a0[2] * g.s[2][i]) * 0.125;
+    double m2 = 0.0, n2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double sm = g.S(k, -1.0), sp = g.S(k, 1.0);
+        m2 = fma(sm, sm, m2);
+        n2 = fma(sp, sp, n2);
+    }
+    g.rm = 1.0 / sqrt(m2);
+    g.rp = 1.0 / sqrt(n2);
+    return g;
+}
+
+// The whole residual in one kernel (metric_lines.h), for states whose elements
+// start on 16-byte boundaries.  Floor 26 values per point and 24 per element
+// (0.71 ms at the rate of a copy for p = 4 on 51^3 hexes); what bounds it is the
+// FP64 and LDS work of a line, which reads all thirteen variables in every
+// direction.  p = 1..6 at the size of 51^3 p = 4: 2.1 1.9 1.8 1.8 1.8 2.4 ms, the
+// three kernels above 5.6 4.5 4.5 3.8 4.1 6.0; on 8^3 hexes 10 to 29 us, 30 to 55.
+template <int P>
+__global__ void __launch_bounds__(dev::MetricShape<P>::NT)
+    k_lh_lines(const double *__restrict__ corners, const double *__restrict__ U, double *__restrict__ R,
+               const double *__restrict__ ops, const double *__restrict__ pts, LhArgs A, dev::Bricks g)
+{
+    using namespace dev;
+    __shared__ __align__(16) double smem[MetricLds<P, double, TrilinearGeo>::size];
+    metric_residual<P, double>(U, R, ops, pts, A.zeta, A.nu, A.invT, A.nx, A.ny, A.nz, g, smem,
+                               [&](int d, int e, int a, int b) {
+                                   return line_metric(corners + (int64_t)e * 24, d, pts[a], pts[b]);
+                               });
+}
+
 unsigned blocks_of(int64_t n) { return (unsigned)((n + TB - 1) / TB); }
 
 }  // namespace
@@ -257,6 +336,7 @@ struct fr_lhex {
     fr_plan *plan = nullptr;
     fr::LhArgs args;
     double *utr = nullptr, *FI = nullptr;
+    double *pts = nullptr;   // the solution points
 };
 
 using namespace fr;
@@ -270,6 +350,12 @@ namespace {
 template <int M>
 int launch_lhex(fr_lhex *h, const double *corners, const double *U, double *R, hipStream_t s)
 {
+    if ((((uintptr_t)U | (uintptr_t)R) & 15) == 0) {
+        const dev::Bricks g = bricks_for(dev::MetricShape<M - 1>::E, 8, h->args.nx, h->args.ny, h->args.nz);
+        hipLaunchKernelGGL(k_lh_lines<M - 1>, dim3((g.nb + 7) / 8 * 8), dim3(dev::MetricShape<M - 1>::NT),
+                           0, s, corners, U, R, (const double *)h->plan->ops64, h->pts, h->args, g);
+        return check_hip(hipGetLastError(), "k_lh_lines launch");
+    }
     constexpr int nfp = M * M, ns = nfp * M;
     const int64_t ne = h->plan->ne;
     const int epb = ns >= 256 ? 1 : 256 / ns;
@@ -311,7 +397,9 @@ fr_lhex *fr_lhex_create(fr_plan *plan)
     A.invT = 1.0 / plan->T;
     const size_t nfp = (size_t)m * m, ne = (size_t)plan->ne;
     if (check_hip(hipMalloc((void **)&h->utr, ne * 6 * NTR * nfp * sizeof(double)), "hipMalloc(lhex traces)") ||
-        check_hip(hipMalloc((void **)&h->FI, ne * 3 * NV * nfp * sizeof(double)), "hipMalloc(lhex fluxes)")) {
+        check_hip(hipMalloc((void **)&h->FI, ne * 3 * NV * nfp * sizeof(double)), "hipMalloc(lhex fluxes)") ||
+        check_hip(hipMalloc((void **)&h->pts, m * sizeof(double)), "hipMalloc(lhex points)") ||
+        check_hip(hipMemcpy(h->pts, A.x, m * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy(lhex points)")) {
         fr_lhex_destroy(h);
         return nullptr;
     }
@@ -341,6 +429,7 @@ void fr_lhex_destroy(fr_lhex *h)
     if (!h) return;
     if (h->utr) (void)hipFree(h->utr);
     if (h->FI) (void)hipFree(h->FI);
+    if (h->pts) (void)hipFree(h->pts);
     delete h;
 }
 
