@@ -73,8 +73,9 @@ typedef enum fr_option {
                              which keeps the separate kernel); 0: residual kernel + separate
                              stage kernel.  The epilogue runs in the residual's own kernel
                              for the point and halo forms (FR_INFO_RESIDUAL_FORM), and then
-                             the states are bitwise identical either way; with the line form
-                             it runs in the point form's kernel (equal to rounding).  The
+                             the states are bitwise identical either way; with the line form,
+                             and with a non-diagonal Jacobian under FR_FORM_AUTO, it runs in
+                             the point form's kernel (equal to rounding).  The
                              norm's summation order (per workgroup) differs.                 */
     FR_OPT_PSEUDO = 8,    /* pseudo-time scheme of fr_dual_step and of every fr_pmg level:
                              0 (default) classical RK4 with the fixed step dtau; 1 the RK34
@@ -96,7 +97,9 @@ typedef enum fr_option {
                              from their states (the batch's tile, else global memory) with
                              the trace kernel's arithmetic, so its results are bitwise those
                              of FR_FORM_LINES; FR_FORM_AUTO (default) the fastest measured:
-                             the halo form with a diagonal Jacobian, else the point form.
+                             the halo form with a diagonal Jacobian, else the point form, for
+                             whose residual larger lattices take one kernel of line tasks in
+                             which each lane forms its neighbours' traces (equal to rounding).
                              The point and line forms agree to rounding (not bitwise); the
                              stage epilogue of fr_rk_step /
                              fr_dual_step uses the halo form's kernel when that is the
@@ -147,7 +150,7 @@ int fr_plan_get_int(const fr_plan *plan, int key, int *value);
 /* Read-only keys of fr_plan_get_int, for the plan's current settings:
  *   FR_INFO_RESIDUAL_FORM  the kernel form fr_residual runs (FR_FORM_POINT,
  *                          FR_FORM_LINES or FR_FORM_HALO; 0 for FR_UNFUSED and
- *                          FR_MFMA)
+ *                          FR_MFMA; FR_FORM_POINT for every non-diagonal Jacobian)
  *   FR_INFO_STAGE_PATH     how fr_rk_step and fr_dual_step (RK4 pseudo-steps)
  *                          apply each stage update: FR_STAGE_SEPARATE (residual
  *                          kernels, then the separate stage kernel),

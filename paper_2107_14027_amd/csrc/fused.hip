@@ -20,7 +20,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "bricks.h"
+#include "metric_lines.h"
 
 namespace fr {
 namespace {
@@ -2184,6 +2184,28 @@ __global__ void __launch_bounds__(FR_TLNT)
     }
 }
 
+// The whole residual in one kernel for a general constant Jacobian
+// (metric_lines.h): no traces in memory and one pass over the state instead of
+// two.  Bound by LDS (a line reads all thirteen variables).  p = 1..6 with some
+// 4 million points in FP64: 0.66 0.69 0.36 0.52 0.54 0.59 ms, the point form 1.07
+// 0.93 0.49 0.62 0.62 0.69; FP32 0.40 0.43 0.16 0.27 0.29 0.34, 0.66 0.53 0.23
+// 0.37 0.42 0.51.
+template <int P, typename T>
+__global__ void __launch_bounds__(MetricShape<P>::NT)
+    k_metric(const T *__restrict__ U, T *__restrict__ R, const T *__restrict__ ops, Consts<T> c, int nx, int ny,
+             int nz, Bricks g)
+{
+    __shared__ __align__(16) T smem[MetricLds<P, T, AffineGeo<T>>::size];
+    metric_residual<P, T>(U, R, ops, ops, c.zeta, c.nu, c.invT, nx, ny, nz, g, smem,
+                          [&](int d, int, int, int) { return AffineGeo<T>(c, d); });
+}
+
+// FR_FORM_AUTO's smallest lattice of a general Jacobian on k_metric: from 4^3 the
+// one launch is ahead (p = 1..4 FP64 9 to 15 us, the two of the point form 18 to
+// 21); from p = 5 on it is even with them up to 8^3 (p = 6 FP64 27.5 and 26.5 us)
+// and ahead from 12^3 (68 and 82).
+template <int P> constexpr int64_t metric_least() { return P >= 5 ? 1000 : 64; }
+
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
@@ -2233,6 +2255,15 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
                                  (pl->form == FR_FORM_AUTO && LinesShape<P, T>::AUTO == 1)));
     if (!MF && !sp && !DIAG && (pl->form == FR_FORM_LINES || pl->form == FR_FORM_HALO))
         return set_error(FR_EUNSUPPORTED, "line-task forms: diagonal Jacobians only");
+    if constexpr (!MF && !DIAG)
+        if (!sp && pl->form == FR_FORM_AUTO && pl->ne >= metric_least<P>() &&
+            (((uintptr_t)U | (uintptr_t)R) & 15) == 0) {
+            const Bricks g = bricks_for(MetricShape<P>::E, sizeof(T), pl->nx, pl->ny, pl->nz);
+            ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
+            hipLaunchKernelGGL((k_metric<P, T>), dim3((g.nb + 7) / 8 * 8), dim3(MetricShape<P>::NT), 0, s, U, R,
+                               ops, c, pl->nx, pl->ny, pl->nz, g);
+            return check_hip(hipGetLastError(), "k_metric launch");
+        }
     // persistent grid: every workgroup that fits on the device at once
     auto persistent_grid = [&](const void *fn, int nt, size_t lds, int &grid) -> int {
         if (grid) return FR_OK;

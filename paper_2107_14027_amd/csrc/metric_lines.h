@@ -374,26 +374,23 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
         constexpr int J = decltype(jc)::value;
         __syncthreads();
         const int k = d + J >= 3 ? d + J - 3 : d + J;
-        auto var = [&](int v) {
-            T *q = X + v * NS;
-#pragma unroll
-            for (int r = 0; r < M; ++r) {
-                T o = part[v][r];
-                if constexpr (J != 0) o += q[r * str];
-                if constexpr (J == 2) o *= -(Geo::constant_det ? geo.inv_det(T(0)) : W[r * str]);
-                q[r * str] = o;
-            }
+        if (!act) return;
+        auto put = [&](T *q, int r, T o) {
+            if constexpr (J != 0) o += q[r * str];
+            if constexpr (J == 2) o *= -(Geo::constant_det ? geo.inv_det(T(0)) : W[r * str]);
+            q[r * str] = o;
         };
-        if (act) {
-            if (k == 0) {
-                var(0);
-                var(1);
-            } else if (k == 1) {
-                var(2);
-            } else {
-                var(3);
-            }
+        // the component is selected, not branched on: of three branches that
+        // differ in their registers alone the compiler (ROCm 7.2) merged the last
+        // stores and left the common factor unset for some lanes (p = 1)
+#pragma unroll
+        for (int r = 0; r < M; ++r) {
+            const T a = part[1][r], b = part[2][r], c = part[3][r];
+            put(X + (1 + k) * NS, r, k == 0 ? a : (k == 1 ? b : c));
         }
+        if (k == 0)
+#pragma unroll
+            for (int r = 0; r < M; ++r) put(X, r, part[0][r]);
     };
     aux(Dir<0>{});
     aux(Dir<1>{});
