@@ -433,8 +433,9 @@ __global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(AcmLin
     const int d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double opv = 0.0;
     if (threadIdx.x < OL::size) opv = ops[threadIdx.x];
+    const BrickElems<(E > 2)> elem(g, cx, cy, cz, A.nx, A.ny, A.nz);
     for (int u = d; u < E * UNITS; u += 3) {
-        const int s = u / UNITS, e = brick_slot(g, s, cx, cy, cz, A.nx, A.ny, A.nz).e;
+        const int s = u / UNITS, e = elem(s);
         if (e >= 0) slot_load<LT>(U + (int64_t)e * RAW, 0, sU + s * LT::SLOT, u - s * UNITS);
     }
     const int lane = threadIdx.x & 63, el = lane / NF, L = lane - el * NF;
@@ -529,7 +530,7 @@ __global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(AcmLin
     if (act && d == 2) add(Dir<2>{});
     __syncthreads();
     for (int u = d; u < E * UNITS; u += 3) {
-        const int s = u / UNITS, e = brick_slot(g, s, cx, cy, cz, A.nx, A.ny, A.nz).e;
+        const int s = u / UNITS, e = elem(s);
         if (e >= 0) slot_store<LT>(sU + s * LT::SLOT, 0, R + (int64_t)e * RAW, u - s * UNITS);
     }
 }

@@ -158,6 +158,27 @@ __device__ __forceinline__ BrickSlot brick_slot(const Bricks &g, int s, int cx, 
     return r;
 }
 
+// The elements of a brick's slots for loops in which a wave goes over the slots:
+// worked out once, slot s in lane s of every wave (working them out per step was
+// more scalar work than the kernel's arithmetic, 1150 scalar to 790 vector
+// instructions a wave at p = 3, and cost 2 to 3 % there).  LANES false: per step
+// after all, for one or two slots, where the lane reads cost 1 %.
+template <bool LANES>
+struct BrickElems {
+    const Bricks &g;
+    const int cx, cy, cz, nx, ny, nz, e;
+    __device__ __forceinline__ BrickElems(const Bricks &g_, int cx_, int cy_, int cz_, int nx_, int ny_, int nz_)
+        : g(g_), cx(cx_), cy(cy_), cz(cz_), nx(nx_), ny(ny_), nz(nz_),
+          e(LANES ? brick_slot(g_, threadIdx.x & 63, cx_, cy_, cz_, nx_, ny_, nz_).e : 0)
+    {
+    }
+    // of the wave's slot s: negative when not in use
+    __device__ __forceinline__ int operator()(int s) const
+    {
+        return LANES ? __builtin_amdgcn_readlane(e, s) : brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+    }
+};
+
 // Workgroup b's brick, or -1.  Consecutive workgroups go to the eight XCDs in
 // turn, each with an L2 of its own.  A group of 8 g.chunk bricks (one layer of
 // the lattice along z) is dealt out so that every XCD works on a contiguous

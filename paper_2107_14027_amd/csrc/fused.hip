@@ -1791,9 +1791,10 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
     T opv = T(0);
     if (threadIdx.x < OL::size) opv = ops[threadIdx.x];
     // the state of the brick's elements into LDS
+    const BrickElems<(E > 1)> elem(g, cx, cy, cz, nx, ny, nz);
     for (int u = wave; u < E * UNITS; u += NT / 64) {
         const int s = u / UNITS;
-        const int e = brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+        const int e = elem(s);
         if (e >= 0) {
             const int lo = LT::off(0, e);
             slot_load<LT>(U + (int64_t)e * RAW, lo, sU + s * LT::SLOT, u - s * UNITS);
@@ -1933,7 +1934,7 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
     if constexpr (STG == STG_NONE) {
         for (int u = wave; u < E * UNITS; u += NT / 64) {
             const int s = u / UNITS;
-            const int e = brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+            const int e = elem(s);
             if (e >= 0) slot_store<LT>(sU + s * LT::SLOT, LT::off(0, e), R + (int64_t)e * RAW, u - s * UNITS);
         }
     } else {
@@ -1942,7 +1943,6 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
         double ss = 0.0;
         constexpr bool LAST = (STG & STG_LAST) != 0, NTS = (STG & STG_STREAM) != 0;
         StageSlots<LAST, NTS, E, NT / 64, line_stage_chunk<P, T, LAST>(), NS, T> stage;
-        auto elem = [&](int s) { return brick_slot(g, s, cx, cy, cz, nx, ny, nz).e; };
         auto tile = [&](int s, int e) -> const T * { return sU + LT::off(s, e); };
 #pragma unroll 1
         for (int u0 = wave; u0 < E * stage.UN; u0 += stage.STEP) {

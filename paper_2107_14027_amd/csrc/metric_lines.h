@@ -320,8 +320,9 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
     const int row = g.by_gx(brick), lay = g.by_gy(row);
     const int cx = (brick - row * g.gx) * g.bx, cy = (row - lay * g.gy) * g.by, cz = lay * g.bz;
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const BrickElems<(E > 1)> elem(g, cx, cy, cz, nx, ny, nz);
     for (int u = wave; u < E * UNITS; u += WAVES) {
-        const int s = u / UNITS, e = brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+        const int s = u / UNITS, e = elem(s);
         if (e >= 0) {
             const int lo = LT::off(0, e);
             slot_load<LT>(U + (int64_t)e * RAW, lo, sU + s * LT::SLOT, u - s * UNITS);
@@ -400,7 +401,7 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
     add(Dir<2>{});
     __syncthreads();
     for (int u = wave; u < E * UNITS; u += WAVES) {
-        const int s = u / UNITS, e = brick_slot(g, s, cx, cy, cz, nx, ny, nz).e;
+        const int s = u / UNITS, e = elem(s);
         if (e >= 0) slot_store<LT>(sU + s * LT::SLOT, LT::off(0, e), R + (int64_t)e * RAW, u - s * UNITS);
     }
 }
