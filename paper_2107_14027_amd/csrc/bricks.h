@@ -207,9 +207,70 @@ struct LinesTile {
     static constexpr int CH = (RAW + (ODD ? VW - 1 : 0) + VW - 1) / VW;   // chunks of a slot
     static constexpr int SLOT = CH * VW;
     static constexpr int OPS = LinesLds<P, T>::OPS;   // the operator block in front of the tile
+    // Where value v of an element lies in its slot.  At m = 4 in FP64 the lines of
+    // x and y start at multiples of 32 and 128 bytes and meet in a quarter of the
+    // banks (47 % of the halo form's LDS cycles were conflicts, 58 % of the general
+    // Jacobian's); in the upper half of z the 16-byte chunks are therefore exchanged
+    // two bits of (x, y) at a time, after which any 16 lines of one direction use
+    // different banks.  Odd m and m = 2, 6 spread by themselves.  General Jacobian
+    // on 40^3 elements 351 -> 314 us, linear hexes on 64^3 1.75 -> 1.63 ms, an RK4
+    // step on 64^3 5.32 -> 5.27 ms, its residual alone (memory-bound) even.
+    static constexpr bool SWZ = P == 3 && sizeof(T) == 8 && NVAR == NV;
+    __device__ __forceinline__ static int place(int v) { return SWZ ? v ^ (v & 32 ? 6 : 0) : v; }
+    __device__ __forceinline__ static int chunk(int c) { return SWZ ? c ^ (c & 16 ? 3 : 0) : c; }
     __device__ __forceinline__ static int off(int slot, int e)
     {
         return slot * SLOT + (ODD ? (int)(((unsigned)e * (unsigned)RAW) % VW) : 0);
+    }
+};
+
+// The direction-D line through face point L in an element's slot Ut of the tile
+// (LT::place): two starting points, from which all m are at fixed distances.
+template <int P, typename T, int D, bool SWZ = LinesTile<P, T>::SWZ>
+struct TileLine {
+    static constexpr int M = P + 1, STR = D == 0 ? 1 : (D == 1 ? M : M * M);
+    int a;
+    __device__ __forceinline__ explicit TileLine(int L) : a(lt_base<P, T, D>(L)) {}
+    __device__ __forceinline__ int at(int l) const { return a + l * STR; }
+    __device__ __forceinline__ void load(const T *Ut, T (&x)[M]) const { line_load<M, STR>(Ut + a, x); }
+    __device__ __forceinline__ void put(T *Ut, const T (&x)[M]) const { line_put<M, STR>(Ut + a, x); }
+};
+template <int P, typename T, int D>
+struct TileLine<P, T, D, true> {
+    static_assert(P == 3 && sizeof(T) == 8, "the exchange of LinesTile");
+    static constexpr int M = 4;
+    int a, b;
+    __device__ __forceinline__ explicit TileLine(int L)
+    {
+        const int x = lt_base<P, T, D>(L);
+        a = x ^ (x & 32 ? 6 : 0);
+        b = a ^ (D == 0 ? 2 : (D == 1 ? 4 : 6));
+    }
+    __device__ __forceinline__ int at(int l) const
+    {
+        return D == 0 ? (l < 2 ? a : b) + (l & 1) : (D == 1 ? (l & 1 ? b : a) + 4 * (l & 2) : (l < 2 ? a : b) + 16 * l);
+    }
+    __device__ __forceinline__ void load(const T *Ut, T (&x)[M]) const
+    {
+        if constexpr (D == 0) {
+            using V = typename V16<T>::type;
+            const V v = *reinterpret_cast<const V *>(Ut + a), w = *reinterpret_cast<const V *>(Ut + b);
+            x[0] = v[0], x[1] = v[1], x[2] = w[0], x[3] = w[1];
+        } else {
+#pragma unroll
+            for (int l = 0; l < M; ++l) x[l] = Ut[at(l)];
+        }
+    }
+    __device__ __forceinline__ void put(T *Ut, const T (&x)[M]) const
+    {
+        if constexpr (D == 0) {
+            using V = typename V16<T>::type;
+            *reinterpret_cast<V *>(Ut + a) = V{x[0], x[1]};
+            *reinterpret_cast<V *>(Ut + b) = V{x[2], x[3]};
+        } else {
+#pragma unroll
+            for (int l = 0; l < M; ++l) Ut[at(l)] = x[l];
+        }
     }
 };
 
@@ -229,7 +290,7 @@ __device__ __forceinline__ void slot_load(const T *__restrict__ src, int lo, T *
     const T *s0 = src - lo;
     const int c0 = unit * 64;
     if (c0 + lane < whole)
-        __builtin_amdgcn_global_load_lds((gptr *)(s0 + (c0 + lane) * LT::VW), (lptr *)(slot + c0 * LT::VW), 16,
+        __builtin_amdgcn_global_load_lds((gptr *)(s0 + LT::chunk(c0 + lane) * LT::VW), (lptr *)(slot + c0 * LT::VW), 16,
                                          0, 0);
     if constexpr (LT::ODD) {
         const int words = ((lo + LT::RAW) % LT::VW) * (int)(sizeof(T) / 4);
@@ -248,7 +309,7 @@ __device__ __forceinline__ void slot_store(const T *slot, int lo, T *__restrict_
     if (c >= LT::CH) return;
     const int v0 = c * LT::VW - lo;                 // first value of the chunk
     if (!LT::ODD || (v0 >= 0 && v0 + LT::VW <= LT::RAW)) {
-        __builtin_nontemporal_store(reinterpret_cast<const V *>(slot)[c], reinterpret_cast<V *>(dst - lo) + c);
+        __builtin_nontemporal_store(reinterpret_cast<const V *>(slot)[LT::chunk(c)], reinterpret_cast<V *>(dst - lo) + c);
     } else {
 #pragma unroll
         for (int w = 0; w < LT::VW; ++w)

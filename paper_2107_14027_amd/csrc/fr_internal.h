@@ -34,6 +34,7 @@ template <int M>
 struct OpsLayout {
     static constexpr int Dt = 0, gl = M * M, gr = M * M + M, lm = M * M + 2 * M,
                          lp = M * M + 3 * M, size = M * M + 4 * M;
+    static constexpr int x = size;   // the solution points, behind the operators
 };
 
 struct Scratch {

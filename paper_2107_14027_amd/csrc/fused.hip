@@ -625,8 +625,8 @@ __device__ __forceinline__ void pair_st(double *p, int v0, double x0, double x1)
 }
 
 // The same for elements that need not follow each other: the residual of
-// element elem(s) (negative: slot not in use) of slot s < E starts at tile(s,
-// elem(s)).  A unit is 64 pairs of values of one element, one pair per lane
+// element elem(s) (negative: slot not in use) of slot s < E is tile(s, elem(s),
+// v) for its value v.  A unit is 64 pairs of values of one element, one pair per lane
 // (16-byte accesses of the double arrays: the pairs start at the element's
 // first 16-byte boundary, so an odd element's first value, or a last one, may
 // be alone in its pair); every wave (of NW) takes C units at a time, from unit
@@ -682,13 +682,12 @@ struct StageSlots {
             const int v0 = ((u - s * UN) * 64 + lane) * 2 - ((e * RAW) & 1);
             if (v0 >= RAW) continue;
             const int64_t g0 = (int64_t)e * RAW;
-            const T *R = tile(s, e);
             double acc[2], next[2];
 #pragma unroll
             for (int w = 0; w < 2; ++w) {
                 const int v = v0 + w;
                 if (v >= 0 && v < RAW)
-                    next[w] = stage_value<T>(sp, LAST, (double)R[v], v >= NS && v < 4 * NS, o[j][w], acc[w], ss);
+                    next[w] = stage_value<T>(sp, LAST, (double)tile(s, e, v), v >= NS && v < 4 * NS, o[j][w], acc[w], ss);
             }
             if constexpr (LAST) pair_st<RAW, NTS>(sp.U + g0, v0, next[0], next[1]);
             else if constexpr (!D64) pair_st<RAW, NTS>(sp.acc + g0, v0, acc[0], acc[1]);
@@ -1550,10 +1549,8 @@ __device__ __forceinline__ void lt_fluxes(T *__restrict__ Ut, const T *__restric
                                           T (&FIm)[NTR], T (&FIp)[NTR])
 {
     constexpr int M = P + 1, NS = M * M * M;
-    constexpr int STR = D == 0 ? 1 : (D == 1 ? M : M * M);
     using OL = OpsLayout<M>;
-    const int base = lt_base<P, T, D>(L);
-    T *Ue = Ut + base;
+    const TileLine<P, T, D> line(L);
     {
         T lm[M], lp[M];
 #pragma unroll
@@ -1565,7 +1562,7 @@ __device__ __forceinline__ void lt_fluxes(T *__restrict__ Ut, const T *__restric
 #pragma unroll
         for (int cc = 0; cc < NTR; ++cc) {
             T x[M];
-            line_load<M, STR>(Ue + (cc < 4 ? cc : 4 + 3 * (cc - 4) + D) * NS, x);
+            line.load(Ut + (cc < 4 ? cc : 4 + 3 * (cc - 4) + D) * NS, x);
             T am = T(0), ap = T(0);
 #pragma unroll
             for (int l = 0; l < M; ++l) {
@@ -1591,12 +1588,12 @@ __device__ __forceinline__ void lt_fluxes(T *__restrict__ Ut, const T *__restric
     {
         T X[3][M], Pl[M];
 #pragma unroll
-        for (int ia = 0; ia < 3; ++ia) line_load<M, STR>(Ue + (1 + ia) * NS, X[ia]);
-        line_load<M, STR>(Ue, Pl);
+        for (int ia = 0; ia < 3; ++ia) line.load(Ut + (1 + ia) * NS, X[ia]);
+        line.load(Ut, Pl);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             T Sl[M];
-            line_load<M, STR>(Ue + (4 + 3 * i + D) * NS, Sl);
+            line.load(Ut + (4 + 3 * i + D) * NS, Sl);
 #pragma unroll
             for (int l = 0; l < M; ++l) {
                 const T vn = X[D][l] * ndd;
@@ -1633,12 +1630,11 @@ template <int P, typename T, int D>
 __device__ __forceinline__ void lt_velocities(const T *__restrict__ Ut, int L, T (&X)[3][P + 1])
 {
     constexpr int M = P + 1, NS = M * M * M;
-    constexpr int STR = D == 0 ? 1 : (D == 1 ? M : M * M);
     __asm__ volatile("" ::: "memory");  // read the velocities again
     __builtin_amdgcn_sched_barrier(0);
-    const T *Ue = Ut + lt_base<P, T, D>(L);
+    const TileLine<P, T, D> line(L);
 #pragma unroll
-    for (int ia = 0; ia < 3; ++ia) line_load<M, STR>(Ue + (1 + ia) * NS, X[ia]);
+    for (int ia = 0; ia < 3; ++ia) line.load(Ut + (1 + ia) * NS, X[ia]);
 }
 
 template <int P, typename T, int D>
@@ -1648,10 +1644,8 @@ __device__ __forceinline__ void lt_derivs(T *__restrict__ Ut, const T *__restric
                                           T (&ctb)[4][P + 1])
 {
     constexpr int M = P + 1, NS = M * M * M;
-    constexpr int STR = D == 0 ? 1 : (D == 1 ? M : M * M);
     using OL = OpsLayout<M>;
-    const int base = lt_base<P, T, D>(L);
-    T *Ue = Ut + base;
+    const TileLine<P, T, D> line(L);
     const T ndd = c.nvec[D][D];
     auto rowV = [&](int r) {
         __builtin_amdgcn_sched_barrier(0);
@@ -1659,7 +1653,7 @@ __device__ __forceinline__ void lt_derivs(T *__restrict__ Ut, const T *__restric
 #pragma unroll
         for (int l = 0; l < M; ++l) Dr[l] = sop[OL::Dt + r * M + l];
         const T glr = sop[OL::gl + r], grr = sop[OL::gr + r];
-        const int q = r * STR;
+        const int q = line.at(r);
         T pc = T(0);
 #pragma unroll
         for (int va = 0; va < 3; ++va) {
@@ -1670,7 +1664,7 @@ __device__ __forceinline__ void lt_derivs(T *__restrict__ Ut, const T *__restric
             const T gv = cd * ndd;
             // S_aD at this point is replaced by the auxiliary residual (only
             // this lane reads or writes it from here on)
-            T *sq = Ue + (4 + 3 * va + D) * NS + q;
+            T *sq = Ut + (4 + 3 * va + D) * NS + q;
             *sq = c.invT * fma(c.inv_det, gv, -*sq);
             if (va == D) pc = fma(c.zeta, gv, fma(glr, FIm[0], grr * FIp[0]));
         }
@@ -1699,6 +1693,23 @@ __device__ __forceinline__ void nbr_trace(const T *__restrict__ Un, int L, const
         T acc = T(0);
 #pragma unroll
         for (int l = 0; l < M; ++l) acc = fma(lf[l], Xc[l * STR], acc);
+        out[cc] = acc;
+    }
+}
+
+// The same from the neighbour's slot of the tile.
+template <int P, typename T, int D>
+__device__ __forceinline__ void tile_trace(const T *__restrict__ Ut, int L, const T *__restrict__ lf,
+                                           T (&out)[NTR])
+{
+    constexpr int M = P + 1, NS = M * M * M;
+    const TileLine<P, T, D> line(L);
+#pragma unroll
+    for (int cc = 0; cc < NTR; ++cc) {
+        const T *Xc = Ut + (cc < 4 ? cc : 4 + 3 * (cc - 4) + D) * NS;
+        T acc = T(0);
+#pragma unroll
+        for (int l = 0; l < M; ++l) acc = fma(lf[l], Xc[line.at(l)], acc);
         out[cc] = acc;
     }
 }
@@ -1862,8 +1873,8 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
         if (offm >= 0 || offp >= 0) {
             auto from_tile = [&](auto dc) {
                 constexpr int DD = decltype(dc)::value;
-                if (offm >= 0) nbr_trace<P, T, DD>(sU + offm, L, sop + OL::lp, othm);
-                if (offp >= 0) nbr_trace<P, T, DD>(sU + offp, L, sop + OL::lm, othp);
+                if (offm >= 0) tile_trace<P, T, DD>(sU + offm, L, sop + OL::lp, othm);
+                if (offp >= 0) tile_trace<P, T, DD>(sU + offp, L, sop + OL::lm, othp);
             };
             if (d == 0) from_tile(Dir<0>{});
             else if (d == 1) from_tile(Dir<1>{});
@@ -1878,8 +1889,7 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
     auto add_lines = [&](auto dc, auto k0c, auto k1c) {
         constexpr int DD = decltype(dc)::value;
         constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
-        constexpr int STR = DD == 0 ? 1 : (DD == 1 ? M : M * M);
-        T *Ue = Ut + lt_base<P, T, DD>(L);
+        const TileLine<P, T, DD> line(L);
 #pragma unroll
         for (int k = K0; k < K1; ++k) {
             T o[M];
@@ -1887,7 +1897,7 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
 #pragma unroll
                 for (int r = 0; r < M; ++r) o[r] = ctb[k][r];
             } else {
-                line_load<M, STR>(Ue + k * NS, o);
+                line.load(Ut + k * NS, o);
 #pragma unroll
                 for (int r = 0; r < M; ++r) o[r] = o[r] + ctb[k][r];
                 if constexpr (DD == 2) {
@@ -1895,7 +1905,7 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
                     for (int r = 0; r < M; ++r) o[r] = mid * o[r];
                 }
             }
-            line_put<M, STR>(Ue + k * NS, o);
+            line.put(Ut + k * NS, o);
         }
     };
     // the momentum parts are summed between the two halves of the line task,
@@ -1943,7 +1953,7 @@ __global__ void __launch_bounds__((LinesShape<P, T>::NT))
         double ss = 0.0;
         constexpr bool LAST = (STG & STG_LAST) != 0, NTS = (STG & STG_STREAM) != 0;
         StageSlots<LAST, NTS, E, NT / 64, line_stage_chunk<P, T, LAST>(), NS, T> stage;
-        auto tile = [&](int s, int e) -> const T * { return sU + LT::off(s, e); };
+        auto tile = [&](int s, int e, int v) { return sU[LT::off(s, e) + LT::place(v)]; };
 #pragma unroll 1
         for (int u0 = wave; u0 < E * stage.UN; u0 += stage.STEP) {
             stage.request(sp, elem, u0);
@@ -2187,8 +2197,8 @@ __global__ void __launch_bounds__(FR_TLNT)
 // The whole residual in one kernel for a general constant Jacobian
 // (metric_lines.h): no traces in memory and one pass over the state instead of
 // two.  Bound by LDS (a line reads all thirteen variables).  p = 1..6 with some
-// 4 million points in FP64: 0.66 0.69 0.36 0.52 0.54 0.59 ms, the point form 1.07
-// 0.93 0.49 0.62 0.62 0.69; FP32 0.40 0.43 0.16 0.27 0.29 0.34, 0.66 0.53 0.23
+// 4 million points in FP64: 0.63 0.68 0.31 0.50 0.52 0.57 ms, the point form 1.07
+// 0.93 0.49 0.62 0.62 0.69; FP32 0.40 0.43 0.16 0.27 0.30 0.34, 0.66 0.53 0.24
 // 0.37 0.42 0.51.
 template <int P, typename T>
 __global__ void __launch_bounds__(MetricShape<P>::NT)
@@ -2196,7 +2206,7 @@ __global__ void __launch_bounds__(MetricShape<P>::NT)
              int nz, Bricks g)
 {
     __shared__ __align__(16) T smem[MetricLds<P, T, AffineGeo<T>>::size];
-    metric_residual<P, T>(U, R, ops, ops, c.zeta, c.nu, c.invT, nx, ny, nz, g, smem,
+    metric_residual<P, T>(U, R, ops, c.zeta, c.nu, c.invT, nx, ny, nz, g, smem,
                           [&](int d, int, int, int) { return AffineGeo<T>(c, d); });
 }
 

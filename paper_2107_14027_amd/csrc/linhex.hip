@@ -312,16 +312,18 @@ __device__ __forceinline__ dev::TrilinearGeo line_metric(const double *__restric
 // start on 16-byte boundaries.  Floor 26 values per point and 24 per element
 // (0.71 ms at the rate of a copy for p = 4 on 51^3 hexes); what bounds it is the
 // FP64 and LDS work of a line, which reads all thirteen variables in every
-// direction.  p = 1..6 at the size of 51^3 p = 4: 2.1 1.9 1.8 1.8 1.8 2.4 ms, the
+// direction.  p = 1..6 at the size of 51^3 p = 4: 2.0 1.9 1.6 1.8 1.8 2.3 ms, the
 // three kernels above 5.6 4.5 4.5 3.8 4.1 6.0; on 8^3 hexes 10 to 29 us, 30 to 55.
 template <int P>
-__global__ void __launch_bounds__(dev::MetricShape<P>::NT)
+__global__ void __launch_bounds__(dev::MetricShape<P>::NT) __attribute__((amdgpu_waves_per_eu(3, 8)))
     k_lh_lines(const double *__restrict__ corners, const double *__restrict__ U, double *__restrict__ R,
-               const double *__restrict__ ops, const double *__restrict__ pts, LhArgs A, dev::Bricks g)
+               const double *__restrict__ ops, double zeta, double nu, double invT, int nx, int ny, int nz,
+               dev::Bricks g)
 {
     using namespace dev;
     __shared__ __align__(16) double smem[MetricLds<P, double, TrilinearGeo>::size];
-    metric_residual<P, double>(U, R, ops, pts, A.zeta, A.nu, A.invT, A.nx, A.ny, A.nz, g, smem,
+    const double *pts = ops + OpsLayout<P + 1>::x;
+    metric_residual<P, double>(U, R, ops, zeta, nu, invT, nx, ny, nz, g, smem,
                                [&](int d, int e, int a, int b) {
                                    return line_metric(corners + (int64_t)e * 24, d, pts[a], pts[b]);
                                });
@@ -336,7 +338,6 @@ struct fr_lhex {
     fr_plan *plan = nullptr;
     fr::LhArgs args;
     double *utr = nullptr, *FI = nullptr;
-    double *pts = nullptr;   // the solution points
 };
 
 using namespace fr;
@@ -353,7 +354,8 @@ int launch_lhex(fr_lhex *h, const double *corners, const double *U, double *R, h
     if ((((uintptr_t)U | (uintptr_t)R) & 15) == 0) {
         const dev::Bricks g = bricks_for(dev::MetricShape<M - 1>::E, 8, h->args.nx, h->args.ny, h->args.nz);
         hipLaunchKernelGGL(k_lh_lines<M - 1>, dim3((g.nb + 7) / 8 * 8), dim3(dev::MetricShape<M - 1>::NT),
-                           0, s, corners, U, R, (const double *)h->plan->ops64, h->pts, h->args, g);
+                           0, s, corners, U, R, (const double *)h->plan->ops64, h->args.zeta, h->args.nu, h->args.invT,
+                           h->args.nx, h->args.ny, h->args.nz, g);
         return check_hip(hipGetLastError(), "k_lh_lines launch");
     }
     constexpr int nfp = M * M, ns = nfp * M;
@@ -397,9 +399,7 @@ fr_lhex *fr_lhex_create(fr_plan *plan)
     A.invT = 1.0 / plan->T;
     const size_t nfp = (size_t)m * m, ne = (size_t)plan->ne;
     if (check_hip(hipMalloc((void **)&h->utr, ne * 6 * NTR * nfp * sizeof(double)), "hipMalloc(lhex traces)") ||
-        check_hip(hipMalloc((void **)&h->FI, ne * 3 * NV * nfp * sizeof(double)), "hipMalloc(lhex fluxes)") ||
-        check_hip(hipMalloc((void **)&h->pts, m * sizeof(double)), "hipMalloc(lhex points)") ||
-        check_hip(hipMemcpy(h->pts, A.x, m * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy(lhex points)")) {
+        check_hip(hipMalloc((void **)&h->FI, ne * 3 * NV * nfp * sizeof(double)), "hipMalloc(lhex fluxes)")) {
         fr_lhex_destroy(h);
         return nullptr;
     }
@@ -429,7 +429,6 @@ void fr_lhex_destroy(fr_lhex *h)
     if (!h) return;
     if (h->utr) (void)hipFree(h->utr);
     if (h->FI) (void)hipFree(h->FI);
-    if (h->pts) (void)hipFree(h->pts);
     delete h;
 }
 

@@ -112,17 +112,35 @@ struct TrilinearGeo {
     }
 };
 
+// The points of a line: at(l) is the place of the l-th in an element's block, in
+// memory (base + l str) or in the tile (LinesTile::place).
+template <int P>
+struct MemoryLine {
+    int base, str;
+    __device__ __forceinline__ int at(int l) const { return base + l * str; }
+};
+template <typename LT, int P>
+struct SlotLine {
+    int p[P + 1];
+    __device__ __forceinline__ SlotLine(int base, int str)
+    {
+#pragma unroll
+        for (int l = 0; l <= P; ++l) p[l] = LT::place(base + l * str);
+    }
+    __device__ __forceinline__ int at(int l) const { return p[l]; }
+};
+
 // The traces of P, u, v, w and of (grad V) n at the end with basis values lf of
-// the line X (first point; points str and variables NS apart).
-template <int P, typename T>
-__device__ __forceinline__ void full_trace(const T *X, int str, OpPtr<T> lf, const T (&nh)[3],
+// the line of the element block X.
+template <int P, typename T, typename Line>
+__device__ __forceinline__ void full_trace(const T *X, const Line &line, OpPtr<T> lf, const T (&nh)[3],
                                            T (&out)[NTR])
 {
     constexpr int M = P + 1, NS = M * M * M;
     auto end = [&](int v) {
         T acc = T(0);
 #pragma unroll
-        for (int l = 0; l < M; ++l) acc = fma(lf[l], X[l * str + v * NS], acc);
+        for (int l = 0; l < M; ++l) acc = fma(lf[l], X[line.at(l) + v * NS], acc);
         return acc;
     };
 #pragma unroll
@@ -143,10 +161,9 @@ __device__ __forceinline__ void full_trace(const T *X, int str, OpPtr<T> lf, con
 // (The tile is not marked restrict: the compiler would keep its values in
 // registers from one loop to the next.)
 // First phase: traces, common fluxes, and the corrected derivatives of the P and
-// momentum fluxes into part[0..3][r].  X: the line's first point in the tile;
-// othm, othp: the neighbours' traces; vm, vp: the mean velocities on its faces.
-template <int P, typename T, typename Geo>
-__device__ __forceinline__ void metric_fluxes(const T *X, int str, OpPtr<T> ops, OpPtr<T> x,
+// momentum fluxes into part[0..3][r].  X: the element's slot of the tile; othm, othp: the neighbours' traces; vm, vp: the mean velocities on its faces.
+template <int P, typename T, typename Line, typename Geo>
+__device__ __forceinline__ void metric_fluxes(const T *X, const Line &line, OpPtr<T> ops, OpPtr<T> x,
                                               const T (&othm)[NTR], const T (&othp)[NTR], const Geo &geo,
                                               T zeta, T nu, T (&vm)[3], T (&vp)[3], T (&part)[4][P + 1])
 {
@@ -164,7 +181,7 @@ __device__ __forceinline__ void metric_fluxes(const T *X, int str, OpPtr<T> ops,
             const T wm = ops[OL::lm + l], wp = ops[OL::lp + l];
 #pragma unroll
             for (int v = 0; v < 13; ++v) {
-                const T q = X[l * str + v * NS];
+                const T q = X[line.at(l) + v * NS];
                 am[v] = fma(wm, q, am[v]);
                 ap[v] = fma(wp, q, ap[v]);
             }
@@ -207,7 +224,7 @@ __device__ __forceinline__ void metric_fluxes(const T *X, int str, OpPtr<T> ops,
     for (int l = 0; l < M; ++l) {
         __asm__ volatile("" ::: "memory");   // one point's values at a time
         __builtin_amdgcn_sched_barrier(0);
-        const T *q = X + l * str;
+        const T *q = X + line.at(l);
         const T xl = x[l];
         const T s[3] = {geo.S(0, xl), geo.S(1, xl), geo.S(2, xl)};
         const T u[3] = {q[NS], q[2 * NS], q[3 * NS]};
@@ -242,10 +259,10 @@ __device__ __forceinline__ void metric_fluxes(const T *X, int str, OpPtr<T> ops,
 
 // Round J of the auxiliary sums: S_ak of component k = (d + J) mod 3 minus the
 // corrected derivative of u_a S_dk over det J; after the last round times -1/T,
-// the auxiliary residual.  X, W: the line's first point in the tile and in the
-// field 1 / det J.
-template <int P, typename T, int J, typename Geo>
-__device__ __forceinline__ void metric_aux(T *X, int str, int d, OpPtr<T> ops, OpPtr<T> x, const T *W,
+// the auxiliary residual.  X: the element's slot of the tile; W: its field
+// 1 / det J.
+template <int P, typename T, int J, typename Line, typename Geo>
+__device__ __forceinline__ void metric_aux(T *X, const Line &line, int d, OpPtr<T> ops, OpPtr<T> x, const T *W,
                                            const Geo &geo, T invT, const T (&vm)[3], const T (&vp)[3])
 {
     constexpr int M = P + 1, NS = M * M * M;
@@ -261,7 +278,7 @@ __device__ __forceinline__ void metric_aux(T *X, int str, int d, OpPtr<T> ops, O
         const T s = Geo::at(c, x[l]);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            G[a][l] = X[l * str + (1 + a) * NS] * s;
+            G[a][l] = X[line.at(l) + (1 + a) * NS] * s;
             pin(G[a][l]);
         }
     }
@@ -272,14 +289,14 @@ __device__ __forceinline__ void metric_aux(T *X, int str, int d, OpPtr<T> ops, O
 #pragma unroll
         for (int l = 0; l < M; ++l) Dr[l] = op[OL::Dt + r * M + l];
         const T glr = op[OL::gl + r] * sm, grr = op[OL::gr + r] * sp;
-        const T w = Geo::constant_det ? geo.inv_det(T(0)) : W[r * str];
+        const T w = Geo::constant_det ? geo.inv_det(T(0)) : W[line.at(r)];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             T s = T(0);
 #pragma unroll
             for (int l = 0; l < M; ++l) s = fma(Dr[l], G[a][l], s);
             s = fma(glr, vm[a], fma(grr, vp[a], s));
-            T *q = Y + r * str + 3 * a * NS;
+            T *q = Y + line.at(r) + 3 * a * NS;
             const T v = fma(-w, s, *q);
             *q = J == 2 ? -invT * v : v;
         }
@@ -305,8 +322,8 @@ struct MetricLds {
 // line of direction d through the element's face point (a, b).
 template <int P, typename T, typename MakeGeo>
 __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__restrict__ R,
-                                                const T *__restrict__ ops_, const T *__restrict__ pts_, T zeta,
-                                                T nu, T invT, int nx, int ny, int nz, const Bricks &g, T *sU,
+                                                const T *__restrict__ ops_, T zeta, T nu, T invT,
+                                                int nx, int ny, int nz, const Bricks &g, T *sU,
                                                 MakeGeo &&make_geo)
 {
     using MS = MetricShape<P>;
@@ -314,7 +331,7 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
     using OL = OpsLayout<P + 1>;
     constexpr int M = P + 1, NS = M * M * M, NF = M * M, E = MS::E;
     constexpr int RAW = LT::RAW, UNITS = (LT::CH + 63) / 64, WAVES = MS::NT / 64;
-    const OpPtr<T> ops = op_ptr(ops_), x = op_ptr(pts_);
+    const OpPtr<T> ops = op_ptr(ops_), x = ops + OL::x;
     const int brick = brick_of(g, blockIdx.x);
     if (brick < 0) return;
     const int row = g.by_gx(brick), lay = g.by_gy(row);
@@ -340,35 +357,37 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
     const bool inm = act && sd > 0, inp = act && sd + 1 < bd && xd + 1 < n;
     // the line: first point and the points' distance
     const int base = d == 0 ? M * L : (d == 1 ? la + M * M * lb : L), str = d == 0 ? 1 : (d == 1 ? M : M * M);
-    T *X = sU + (act ? LT::off(el, me.e) : 0) + base;
-    T *W = sU + MetricLds<P, T, AffineGeo<T>>::size + (act ? el : 0) * NS + base;
+    const MemoryLine<P> outer{base, str};
+    const std::conditional_t<LT::SWZ, SlotLine<LT, P>, MemoryLine<P>> inner{base, str};
+    T *X = sU + (act ? LT::off(el, me.e) : 0);
+    T *W = sU + MetricLds<P, T, AffineGeo<T>>::size + (act ? el : 0) * NS;
     const auto geo = make_geo(d, act ? me.e : 0, la, lb);
     using Geo = std::decay_t<decltype(geo)>;
     if constexpr (!Geo::constant_det)
         if (act && d == 0)
 #pragma unroll 1
-            for (int r = 0; r < M; ++r) W[r] = geo.inv_det(x[r]);
+            for (int r = 0; r < M; ++r) W[LT::place(base + r)] = geo.inv_det(x[r]);
     T othm[NTR], othp[NTR];
     {
         T nm[3], np[3];
         geo.template normal<false>(nm);
         geo.template normal<true>(np);
-        if (act && !inm) full_trace<P, T>(U + (int64_t)nbm * RAW + base, str, ops + OL::lp, nm, othm);
-        if (act && !inp) full_trace<P, T>(U + (int64_t)nbp * RAW + base, str, ops + OL::lm, np, othp);
+        if (act && !inm) full_trace<P, T>(U + (int64_t)nbm * RAW, outer, ops + OL::lp, nm, othm);
+        if (act && !inp) full_trace<P, T>(U + (int64_t)nbp * RAW, outer, ops + OL::lm, np, othp);
         // the direct loads into LDS have arrived (their count is not tracked by
         // the barrier)
         __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if constexpr (E > 1) {
-            if (inm) full_trace<P, T>(sU + LT::off(el - ls, nbm) + base, str, ops + OL::lp, nm, othm);
-            if (inp) full_trace<P, T>(sU + LT::off(el + ls, nbp) + base, str, ops + OL::lm, np, othp);
+            if (inm) full_trace<P, T>(sU + LT::off(el - ls, nbm), inner, ops + OL::lp, nm, othm);
+            if (inp) full_trace<P, T>(sU + LT::off(el + ls, nbp), inner, ops + OL::lm, np, othp);
         }
     }
     T vm[3], vp[3], part[4][M];
-    if (act) metric_fluxes<P, T>(X, str, ops, x, othm, othp, geo, zeta, nu, vm, vp, part);
+    if (act) metric_fluxes<P, T>(X, inner, ops, x, othm, othp, geo, zeta, nu, vm, vp, part);
     auto aux = [&](auto jc) {
         __syncthreads();
-        if (act) metric_aux<P, T, decltype(jc)::value>(X, str, d, ops, x, W, geo, invT, vm, vp);
+        if (act) metric_aux<P, T, decltype(jc)::value>(X, inner, d, ops, x, W, geo, invT, vm, vp);
     };
     // round 0 stores, 1 adds, 2 adds and divides by -det J; P goes with u
     auto add = [&](auto jc) {
@@ -377,9 +396,9 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
         const int k = d + J >= 3 ? d + J - 3 : d + J;
         if (!act) return;
         auto put = [&](T *q, int r, T o) {
-            if constexpr (J != 0) o += q[r * str];
-            if constexpr (J == 2) o *= -(Geo::constant_det ? geo.inv_det(T(0)) : W[r * str]);
-            q[r * str] = o;
+            if constexpr (J != 0) o += q[inner.at(r)];
+            if constexpr (J == 2) o *= -(Geo::constant_det ? geo.inv_det(T(0)) : W[inner.at(r)]);
+            q[inner.at(r)] = o;
         };
         // the component is selected, not branched on: of three branches that
         // differ in their registers alone the compiler (ROCm 7.2) merged the last

@@ -331,11 +331,15 @@ fr_plan *fr_plan_create(int p, int nx, int ny, int nz, const double jac[9], doub
         delete pl;
         return nullptr;
     }
-    const int nops = pl->m * pl->m + 4 * pl->m;
+    const int nops = pl->m * pl->m + 5 * pl->m;   // OpsLayout and, behind it, the points
     double h64[128];
     float h32[128];
     pack_ops(pl, h64);
     pack_ops(pl, h32);
+    for (int i = 0; i < pl->m; ++i) {
+        h64[nops - pl->m + i] = pl->x[i];
+        h32[nops - pl->m + i] = (float)pl->x[i];
+    }
     if (check_hip(hipMalloc(&pl->ops64, nops * sizeof(double)), "hipMalloc(ops64)") ||
         check_hip(hipMalloc(&pl->ops32, nops * sizeof(float)), "hipMalloc(ops32)") ||
         check_hip(hipMemcpy(pl->ops64, h64, nops * sizeof(double), hipMemcpyHostToDevice),
