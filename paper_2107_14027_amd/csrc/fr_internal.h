@@ -120,9 +120,9 @@ struct fr_plan {
     // (order, precision, diagonal Jacobian): [0] trace kernel, [1] fused kernel,
     // [2] fused kernel with the stage epilogue, [3] its matrix-core form
     int fused_grid[4][fr::PMAX + 1][2][2] = {};
-    // 1 once the LDS limit of the line-form kernels is set on this plan's
-    // device, per (kernel: 0 residual, 1 traces; order; precision)
-    int lines_attr[2][fr::PMAX + 1][2] = {};
+    // 1 once the LDS limit of the line-form trace kernel is set on this plan's
+    // device, per (order, precision)
+    int lines_attr[fr::PMAX + 1][2] = {};
     // 1 once the LDS limit of the unfused stage-1 kernel is set (order, precision)
     int unfused_attr[fr::PMAX + 1][2] = {};
     int device;

@@ -474,15 +474,14 @@ template <int P, bool DIAG> struct LineDiv {
 // Values per thread whose global operands the stage epilogue requests at once,
 // per order and precision (a larger chunk overlaps more loads but can cost a
 // wave of occupancy; measured).  FR_STG_CHUNK overrides the table.
-template <int P, typename T>
+template <int P, typename T, bool DIAG>
 constexpr int stage_chunk()
 {
 #ifdef FR_STG_CHUNK
     return FR_STG_CHUNK;
 #else
-    constexpr int d[PMAX + 1] = {0, 1, 1, 8, 1, 8, 4};
-    constexpr int f[PMAX + 1] = {0, 8, 4, 1, 1, 8, 1};
-    return sizeof(T) == 8 ? d[P] : f[P];
+    constexpr int d[PMAX + 1] = {0, 6, 6, 8, 4, 6, 6};
+    return sizeof(T) == 4 || (P == 5 && !DIAG) ? 4 : d[P];
 #endif
 }
 
@@ -548,9 +547,11 @@ __device__ __forceinline__ bool stage_reads_acc(const StageSpec &sp)
 // chunk are requested before the first is used, so that the loads of a wave
 // overlap, with a bounded register cost.  With tr_out the produced state
 // replaces the residual in the tile.
-template <int J, int C, int NS, typename T, bool NTS, typename Tile>
-__device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&tile, unsigned tid,
-                                                   unsigned nt, unsigned cnt, int64_t e0, double &ss)
+// (LAST and the two uses of the BDF source are told apart outside the loops:
+// decided per value they cost 15-30 % of a stage.)
+template <int J, int C, int NS, typename T, bool NTS, bool LAST, bool BDF, typename Tile>
+__device__ __forceinline__ void stage_update_as(const StageSpec &sp, Tile &&tile, unsigned tid,
+                                                unsigned nt, unsigned cnt, int64_t e0, double &ss)
 {
     constexpr bool D64 = sizeof(T) == 8;
     const int64_t g0 = e0 * NV * NS;
@@ -563,17 +564,21 @@ __device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&t
             const unsigned t = tid + (j0 + j) * nt;
             if (t < cnt) {
                 const int64_t gi = g0 + t;
-                const unsigned r = t / NS, q = t - r * NS;
-                const unsigned el = r / NV, v = r - el * NV;
-                const bool vel = sp.B && v >= 1 && v <= 3;
-                if (D64 || !sp.last || sp.first) o[j].u = stg_ld<NTS>(sp.U + gi);
+                if (D64 || !LAST || sp.first) o[j].u = stg_ld<NTS>(sp.U + gi);
                 if (stage_reads_acc<T>(sp)) o[j].acc = stg_ld<NTS>(sp.acc + gi);
-                if (D64 && sp.last) {
+                if constexpr (D64 && LAST) {
                     o[j].s2 = stg_ld<NTS>(sp.s2 + gi);
                     o[j].s3 = stg_ld<NTS>(sp.s3 + gi);
+                    o[j].s = stg_ld<NTS>(sin + gi);
                 }
-                if (vel || (D64 && sp.last)) o[j].s = stg_ld<NTS>(sin + gi);
-                if (vel) o[j].b = stg_ld<NTS>(sp.B + ((int64_t)(e0 + el) * 3 + (v - 1)) * NS + q);
+                if constexpr (BDF) {
+                    const unsigned r = t / NS, q = t - r * NS;
+                    const unsigned el = r / NV, v = r - el * NV;
+                    if (v >= 1 && v <= 3) {
+                        if (!(D64 && LAST)) o[j].s = stg_ld<NTS>(sin + gi);
+                        o[j].b = stg_ld<NTS>(sp.B + ((int64_t)(e0 + el) * 3 + (v - 1)) * NS + q);
+                    }
+                }
                 if (sp.D) o[j].d = stg_ld<NTS>(sp.D + gi);
             }
         }
@@ -585,14 +590,26 @@ __device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&t
                 const unsigned v = (t / NS) % NV;
                 const bool vel = v >= 1 && v <= 3;
                 double acc;
-                const double next = stage_value<T>(sp, sp.last, (double)tile(t), vel, o[j], acc, ss);
-                if (sp.last) stg_st<NTS>(sp.U + gi, next);
+                const double next = stage_value<T>(sp, LAST, (double)tile(t), vel, o[j], acc, ss);
+                if (LAST) stg_st<NTS>(sp.U + gi, next);
                 else if (!D64) stg_st<NTS>(sp.acc + gi, acc);
-                if (vel && sp.s_out64) stg_st<NTS>(sp.s_out64 + gi, next);
+                if (BDF && sp.s_out64 && vel) stg_st<NTS>(sp.s_out64 + gi, next);
                 if (sp.s_out) stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)next);
                 if (sp.tr_out) tile(t) = (T)next;
             }
         }
+    }
+}
+template <int J, int C, int NS, typename T, bool NTS, typename Tile>
+__device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&tile, unsigned tid,
+                                                   unsigned nt, unsigned cnt, int64_t e0, double &ss)
+{
+    if (sp.last) {
+        if (sp.B) stage_update_as<J, C, NS, T, NTS, true, true>(sp, tile, tid, nt, cnt, e0, ss);
+        else stage_update_as<J, C, NS, T, NTS, true, false>(sp, tile, tid, nt, cnt, e0, ss);
+    } else {
+        if (sp.B) stage_update_as<J, C, NS, T, NTS, false, true>(sp, tile, tid, nt, cnt, e0, ss);
+        else stage_update_as<J, C, NS, T, NTS, false, false>(sp, tile, tid, nt, cnt, e0, ss);
     }
 }
 
@@ -1185,7 +1202,7 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
             //      are requested before the first is used, so that the loads of a
             //      wave overlap, with a bounded register cost.
             constexpr int J = (EMAX * NV * NS + NT - 1) / NT;
-            constexpr int C = stage_chunk<P, T>() < J ? stage_chunk<P, T>() : J;
+            constexpr int C = stage_chunk<P, T, DIAG>() < J ? stage_chunk<P, T, DIAG>() : J;
             __syncthreads();
             stage_update_batch<J, C, NS, T, P != 4>(sp, [&](unsigned t) -> T & { return sU[t]; }, tid, NT,
                                            (unsigned)nel * NV * NS, e0, ss);
@@ -1295,8 +1312,8 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 // thread) while the neighbours' lines are read, and XCD k works on a contiguous
 // eighth of a layer (brick_of).  Before and after, whole residual, ms, on the
 // order-sweep lattices:
-//   double  p = 1..6  0.93 1.05 0.91 1.23 1.29 1.52 -> 0.85 0.94 0.84 0.98 1.04 1.25
-//   single  p = 1..6  0.55 0.62 0.44 0.66 0.70 0.84 -> 0.53 0.56 0.40 0.52 0.54 0.68
+//   double  p = 1..6  0.93 1.05 0.91 1.23 1.29 1.52 -> 0.82 0.91 0.80 0.94 1.07 1.24
+//   single  p = 1..6  0.55 0.62 0.44 0.66 0.70 0.84 -> 0.49 0.56 0.39 0.50 0.53 0.68
 // More waves by spilling (a waves-per-SIMD hint), workgroups of more waves (E and
 // LW doubled) and bricks ordered in pencils measured slower or equal.
 // ---------------------------------------------------------------------------
@@ -2295,7 +2312,8 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
     };
     int &grid_tr = pl->fused_grid[0][P][sizeof(T) == 8][DIAG];
     int &grid_fu = pl->fused_grid[MF ? 3 : (sp ? 2 : 1)][P][sizeof(T) == 8][DIAG];
-    if (int rc = persistent_grid(ktr, TNT, lds_tr, grid_tr)) return rc;
+    if (!halo)
+        if (int rc = persistent_grid(ktr, TNT, lds_tr, grid_tr)) return rc;
     if (!lines && !halo)
         if (int rc = persistent_grid(kfu, NT, lds_fu, grid_fu)) return rc;
     const unsigned gtr = (unsigned)min(nbatch_tr, grid_tr);
@@ -2309,7 +2327,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
     } else if (DIAG && TraceLinesShape<P, T>::USE) {
         using TLS = TraceLinesShape<P, T>;
         const size_t lds_tl = (size_t)TLS::values * sizeof(T);
-        int &set = pl->lines_attr[1][P][sizeof(T) == 8];
+        int &set = pl->lines_attr[P][sizeof(T) == 8];
         if (!set) {
             if (int rc = check_hip(hipFuncSetAttribute((const void *)k_trace_lines<P, T>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2330,23 +2348,11 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
         constexpr int LE = LinesShape<P, T>::E, LNT = LinesShape<P, T>::NT;
         using LT = LinesTile<P, T>;
         constexpr size_t lds_li = ((size_t)LT::OPS + (size_t)LE * LT::SLOT) * sizeof(T);
-        static_assert(lds_li <= 160 * 1024, "LDS");
+        // (what a launch may ask for without hipFuncSetAttribute: six calls of it
+        // were a good part of a plan's first residual on a small lattice)
+        static_assert(lds_li <= 64 * 1024, "LDS");
         const Bricks g = bricks_for(LE, sizeof(T), pl->nx, pl->ny, pl->nz);
         const unsigned blocks = (g.nb + 7) / 8 * 8;
-        int &set = pl->lines_attr[0][P][sizeof(T) == 8];
-        if (!set) {
-            for (const void *fn : {(const void *)k_lines<P, T, false, STG_NONE>,
-                                   (const void *)k_lines<P, T, true, STG_NONE>,
-                                   (const void *)k_lines<P, T, true, STG_MID>,
-                                   (const void *)k_lines<P, T, true, STG_LAST>,
-                                   (const void *)k_lines<P, T, true, STG_MID | STG_STREAM>,
-                                   (const void *)k_lines<P, T, true, STG_LAST | STG_STREAM>})
-                if (int rc = check_hip(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                           (int)lds_li),
-                                       "hipFuncSetAttribute"))
-                    return rc;
-            set = 1;
-        }
         ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
         if constexpr (DIAG) {
             if (sp) {
