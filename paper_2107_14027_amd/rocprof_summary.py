@@ -27,7 +27,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("fused.hip", "fr_device.h", "fr_internal.h"):
+    for f in ("fused.hip", "bricks.h", "metric_lines.h", "fr_device.h", "fr_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_2107_14027_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -37,12 +37,13 @@ def short(name):
     if m:
         kern, p, t, extra = m.groups()
         # k_fused<P, T, DIAG, STG[, MF]>: STG selects the stage epilogue;
-        # k_lines<P, T, HALO>: HALO forms the neighbour traces from their states
+        # k_lines<P, T, HALO, STG>: HALO forms the neighbour traces from their
+        # states, STG != 0 applies an RK stage update
         args = [a.strip() for a in extra.split(",") if a.strip()]
         if kern == "k_fused" and len(args) >= 2 and args[1] == "true":
             kern = "k_fused_stage"
         if kern == "k_lines" and args and args[0] == "true":
-            kern = "k_lines_halo"
+            kern = "k_lines_halo" + ("_stage" if args[1:] and args[1] not in ("0", "false") else "")
         return "%s<%s,%s>" % (kern, p, t)
     m = re.search(r"(k_\w+)<([^>]*)>", name)
     if m:
@@ -111,7 +112,7 @@ def traffic(args):
     fs, fcal, fk, fn = res["FETCH_SIZE"]
     ws, wcal, wk, wn = res["WRITE_SIZE"]
     for k in sorted(set(fk) & set(wk)):
-        m = re.match(r"(k_fused|k_trace|k_lines|k_lines_halo|k_trace_lines|k_fused_stage)<(\d+),(\w+)>", k)
+        m = re.match(r"(k_fused|k_trace|k_lines|k_lines_halo|k_lines_halo_stage|k_trace_lines|k_fused_stage)<(\d+),(\w+)>", k)
         if not m:
             continue
         tag = "%s_p%s_%s" % (m.group(1), m.group(2), "f64" if m.group(3) == "double" else "f32")
