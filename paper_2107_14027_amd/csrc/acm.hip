@@ -305,20 +305,22 @@ __device__ __forceinline__ double dot(const double *__restrict__ w, const double
 }
 
 // Common flux through a face of direction D between L (minus side) and R, with
-// the common viscous flux fv, times the face scaling nmag.
+// the common viscous flux fv along e_D, times the face scaling.  The unit normal
+// is e_D or, with a negative Jacobian entry, -e_D: what is linear in it takes the
+// signed n_D, the jump terms its length.
 template <int D>
 __device__ __forceinline__ void acm_face(const double (&L)[NA], const double (&R)[NA],
                                          const double (&fv)[3], const AcmArgs &A, double (&out)[NA])
 {
-    const double vL = L[1 + D], vR = R[1 + D], n = A.nmag[D];
+    const double vL = L[1 + D], vR = R[1 + D], n = A.nmag[D], ns = A.nvec[4 * D];
     const double lam = fmax(fabs(vL) + sqrt(fma(vL, vL, A.zeta)), fabs(vR) + sqrt(fma(vR, vR, A.zeta)));
-    out[0] = n * (0.5 * A.zeta * (vL + vR) - 0.5 * lam * (R[0] - L[0]));
+    out[0] = ns * (0.5 * A.zeta * (vL + vR)) - n * (0.5 * lam * (R[0] - L[0]));
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         double mL = L[1 + c] * vL, mR = R[1 + c] * vR;
         if (c == D) mL += L[0], mR += R[0];
-        out[1 + c] = n * (0.5 * (mL + mR) - 0.5 * lam * (R[1 + c] - L[1 + c]) + fv[c] +
-                          A.tau * (L[1 + c] - R[1 + c]));
+        out[1 + c] = ns * (0.5 * (mL + mR) + fv[c]) -
+                     n * (0.5 * lam * (R[1 + c] - L[1 + c]) - A.tau * (L[1 + c] - R[1 + c]));
     }
 }
 
