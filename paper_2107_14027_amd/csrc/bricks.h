@@ -19,6 +19,22 @@ __device__ __forceinline__ void pin(T &x)
     __asm__ volatile("" : "+v"(x));
 }
 
+// nu with the sign of n (its unit normal's only entry, 1 or -1) on a face of a
+// diagonal Jacobian: the viscous part of the common flux for traces that are S_id
+// (trace_value).  On the bits, so that the sign of a kernel argument stays in the
+// scalar unit (held as three more arguments, or multiplied, it cost p = 6 in
+// double, which is at its register limit, 1.7 % of its residual).
+__device__ __forceinline__ double signed_nu(double nu, double n)
+{
+    const int64_t s = __builtin_bit_cast(int64_t, n) & INT64_MIN;
+    return __builtin_bit_cast(double, __builtin_bit_cast(int64_t, nu) ^ s);
+}
+__device__ __forceinline__ float signed_nu(float nu, float n)
+{
+    const int32_t s = __builtin_bit_cast(int32_t, n) & INT32_MIN;
+    return __builtin_bit_cast(float, __builtin_bit_cast(int32_t, nu) ^ s);
+}
+
 // Common normal flux through a face of direction d, evaluated by the element
 // on one side: own = its trace, oth = the neighbour's, own_minus = the element
 // is on the minus side of the face (its + face).  Equal, bit for bit, to the

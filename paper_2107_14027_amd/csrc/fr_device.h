@@ -49,10 +49,10 @@ __device__ __forceinline__ void line_of(int d, int a, int b, int &base, int &str
 // Written as one explicit fma chain so that every kernel that computes the
 // same trace value produces the same bits.
 //
-// With diag (the reference-face normals are the coordinate axes: a diagonal
-// Jacobian) (S n_hat)_i = S_id exactly, and the product with the unit normal is
-// skipped; the result has the same bits as the general expression, whose other
-// terms are exact zeros and whose product with 1 is exact.
+// With diag (a diagonal Jacobian: the unit normal is e_d or, where J_dd < 0,
+// -e_d) the product with the normal is skipped and c = 4..6 are S_id, with the
+// same bits as the general expression but for that sign, which the common flux
+// applies (signed_nu).
 // VS is the distance between consecutive variables of Ue (m^3 unless the
 // caller pads its lines).
 template <int M, typename T, int VS = M * M * M>

@@ -759,13 +759,16 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
     T *sF = sU + EMAX * NV * NS;
     T *sFI = sF + EMAX * 9 * NS;
     T *sop = sFI + 6 * EMAX * CHP;
-    T *geo = sop + OL::size;  // n_d (row d), n_hat_d (row d), |n_d|
+    T *geo = sop + OL::size;  // n_d (row d), n_hat_d (row d), |n_d|, nu with n_hat_dd's sign
     for (int t = threadIdx.x; t < OL::size; t += NT) sop[t] = ops[t];
     if (threadIdx.x < 9) {
         geo[threadIdx.x] = c.nvec[threadIdx.x / 3][threadIdx.x % 3];
         geo[9 + threadIdx.x] = c.nhat[threadIdx.x / 3][threadIdx.x % 3];
     }
-    if (threadIdx.x < 3) geo[18 + threadIdx.x] = c.nmag[threadIdx.x];
+    if (threadIdx.x < 3) {
+        geo[18 + threadIdx.x] = c.nmag[threadIdx.x];
+        geo[21 + threadIdx.x] = signed_nu(c.nu, c.nhat[threadIdx.x][threadIdx.x]);
+    }
 
     StateStage<T, EMAX * NV * NS, NT> st;
     TraceStage<M, T, EMAX, NT> tt;
@@ -859,7 +862,7 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
             T *slot = sFI + ((2 * d + s) * EMAX + el) * CHP + fp;
 #pragma unroll
             for (int cc = 0; cc < NTR; ++cc) oth[cc] = slot[cc * NF];
-            common_flux_sided<T>(own, oth, s != 0, nh, geo[18 + d], c.zeta, c.nu, out);
+            common_flux_sided<T>(own, oth, s != 0, nh, geo[18 + d], c.zeta, DIAG ? geo[21 + d] : c.nu, out);
 #pragma unroll
             for (int cc = 0; cc < NTR; ++cc) slot[cc * NF] = out[cc];
         }
@@ -1590,8 +1593,9 @@ __device__ __forceinline__ void lt_fluxes(T *__restrict__ Ut, const T *__restric
             ownp[cc] = ap;
         }
         const T nh[3] = {c.nhat[D][0], c.nhat[D][1], c.nhat[D][2]};
-        common_flux_sided<T>(ownm, othm, false, nh, c.nmag[D], c.zeta, c.nu, FIm);
-        common_flux_sided<T>(ownp, othp, true, nh, c.nmag[D], c.zeta, c.nu, FIp);
+        const T nu = signed_nu(c.nu, nh[D]);
+        common_flux_sided<T>(ownm, othm, false, nh, c.nmag[D], c.zeta, nu, FIm);
+        common_flux_sided<T>(ownp, othp, true, nh, c.nmag[D], c.zeta, nu, FIp);
     }
     // the lines are read again below rather than kept live through the
     // common-flux arithmetic (the barrier stops the compiler from reusing the
