@@ -33,23 +33,6 @@ int residual(fr_plan *pl, const void *U, void *R, hipStream_t s)
     return launch_residual(pl, U, R, s);
 }
 
-struct RkBufs {
-    double *acc;
-    void *stT;
-    void *k;
-};
-
-int rk_buffers(fr_plan *pl, RkBufs &b)
-{
-    const size_t n = fr_state_len(pl);
-    const size_t bytes = n * 8 + 2 * n * esize(pl);
-    if (int rc = ensure_scratch(pl->rk, bytes)) return rc;
-    b.acc = (double *)pl->rk.ptr;
-    b.stT = (char *)pl->rk.ptr + n * 8;
-    b.k = (char *)b.stT + n * esize(pl);
-    return FR_OK;
-}
-
 // Stage k (0..3) of a classical RK4 (pseudo-)step of size h on the separate
 // path: the residual, then the stage kernel.  In double the stage states
 // replace the residuals: s2 is in stT, s3 in k, s4 in acc.
@@ -142,6 +125,26 @@ int launch_residual(fr_plan *pl, const void *U, void *R, hipStream_t s)
     return set_error(FR_EINVAL, "variant %d", pl->variant);
 }
 
+int rk_buffers(fr_plan *pl, RkBufs &b)
+{
+    const size_t n = fr_state_len(pl), acc = scratch_bytes(n * 8), state = scratch_bytes(n * esize(pl));
+    if (int rc = ensure_scratch(pl->rk, acc + 2 * state)) return rc;
+    b.acc = (double *)pl->rk.ptr;
+    b.stT = (char *)pl->rk.ptr + acc;
+    b.k = (char *)b.stT + state;
+    return FR_OK;
+}
+
+int dual_buffers(fr_plan *pl, double *&B, double *&st64)
+{
+    const size_t bdf = scratch_bytes((size_t)pl->ne * 3 * pl->m * pl->m * pl->m * 8);
+    const bool f64 = pl->precision == FR_F64;
+    if (int rc = ensure_scratch(pl->dual, bdf + (f64 ? 0 : fr_state_len(pl) * 8))) return rc;
+    B = (double *)pl->dual.ptr;
+    st64 = f64 ? nullptr : (double *)((char *)pl->dual.ptr + bdf);
+    return FR_OK;
+}
+
 int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const double *D,
                    double dtau, double tol, int max_iters, int check_every, bool norm_last,
                    int *iters, double *resid, int *converged, hipStream_t s)
@@ -151,18 +154,15 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
     const int ns = pl->m * pl->m * pl->m;
     RkBufs b;
     if (int rc = rk_buffers(pl, b)) return rc;
-    const size_t nB = (size_t)pl->ne * 3 * ns;
-    // the double copy of the stage state the BDF term needs (FP32) follows the
-    // BDF constant's slot in the plan's dual scratch
+    double *bdf = nullptr, *st64 = nullptr;
     if (!f64)
-        if (int rc = ensure_scratch(pl->dual, (nB + (size_t)n) * sizeof(double))) return rc;
+        if (int rc = dual_buffers(pl, bdf, st64)) return rc;
     const int cap = std::max(std::max(stage_blocks(n), MAX_PARTIALS), stage_partials(pl));
     if (int rc = ensure_scratch(pl->norm, (size_t)(cap + 1) * sizeof(double))) return rc;
     if (!pl->norm_host &&
         check_hip(hipHostMalloc((void **)&pl->norm_host, sizeof(double), hipHostMallocDefault),
                   "hipHostMalloc"))
         return FR_ENOMEM;
-    double *st64 = f64 ? nullptr : (double *)pl->dual.ptr + nB;
     // the RK34 stage kernel's double copy of the stage state
     double *rk34_st64 = f64 ? (double *)b.stT : st64;
     double *partial = (double *)pl->norm.ptr;
@@ -436,11 +436,8 @@ int fr_dual_step(fr_plan *pl, double *U, const double *Un, const double *Unm1, d
         return set_error(FR_EINVAL, "fr_dual_step: dt=%g dtau=%g tol=%g max_iters=%d every=%d", dt,
                          dtau, tol, max_iters, check_every);
     hipStream_t s = (hipStream_t)sv;
-    const bool f64 = pl->precision == FR_F64;
-    const size_t n = fr_state_len(pl);
-    const size_t nB = (size_t)pl->ne * 3 * pl->m * pl->m * pl->m;
-    if (int rc = ensure_scratch(pl->dual, (nB + (f64 ? 0 : n)) * sizeof(double))) return rc;
-    double *B = (double *)pl->dual.ptr;
+    double *B = nullptr, *st64 = nullptr;
+    if (int rc = dual_buffers(pl, B, st64)) return rc;
     if (int rc = launch_bdf_const(pl, Un, Unm1, dt, B, s)) return rc;
     int conv = 0;
     const int rc = pseudo_iterate(pl, U, B, Unm1 ? 1.5 / dt : 1.0 / dt, nullptr, dtau, tol,
@@ -490,12 +487,9 @@ int fr_mlp_guess_checked(fr_plan *pl, const float *state, const double *Un, cons
         overlap(G, bytes, Unm2, bytes))
         return set_error(FR_EINVAL, "fr_mlp_guess_checked: G overlaps an input");
     hipStream_t s = (hipStream_t)sv;
-    const bool f64 = pl->precision == FR_F64;
-    const size_t nB = (size_t)pl->ne * 3 * pl->m * pl->m * pl->m;
     if (int rc = ensure_scratch(pl->guess, bytes)) return rc;
-    if (int rc = ensure_scratch(pl->dual, (nB + (f64 ? 0 : n)) * sizeof(double))) return rc;
-    double *E = (double *)pl->guess.ptr;
-    double *B = (double *)pl->dual.ptr;
+    double *E = (double *)pl->guess.ptr, *B = nullptr, *st64 = nullptr;
+    if (int rc = dual_buffers(pl, B, st64)) return rc;
     // the extrapolation the network corrects, and the network's guess
     if (int rc = launch_extrap(Un, Unm1, Unm2, pl->guess_base, 0, E, (int64_t)n, s)) return rc;
     if (int rc = fr_mlp_guess(pl, state, Un, Unm1, Unm2, G, sv)) return rc;

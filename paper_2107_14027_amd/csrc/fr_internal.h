@@ -136,8 +136,8 @@ struct fr_plan {
     fr::Scratch traces;     // [6][ne][7][m^2] of the working precision
     fr::Scratch traces2;    // second trace array: the stage epilogue's ping-pong
     fr::Scratch unfused;    // stage buffers of the unfused pipeline
-    fr::Scratch rk;         // acc (double), stage (T), k (T)
-    fr::Scratch dual;       // BDF constant part (double, velocity only)
+    fr::Scratch rk;         // RkBufs
+    fr::Scratch dual;       // BDF constant part (double, velocity only), FP32: stage velocities (double)
     fr::Scratch norm;       // partial sums (double)
     fr::Scratch mlp;        // MLP gradient partials / moments
     fr::Scratch diag;       // partial sums of the flow diagnostics
@@ -156,6 +156,11 @@ namespace fr {
 int set_error(int code, const char *fmt, ...);
 int check_hip(hipError_t e, const char *what);
 int ensure_scratch(Scratch &s, size_t bytes);
+// bytes of an array that another one follows in the same scratch: every array
+// starts on a 256-byte boundary (the kernels' 16-byte accesses need 16; an odd
+// number of values, even order on an odd number of elements, would leave 4, 8
+// or 12 over)
+inline size_t scratch_bytes(size_t bytes) { return (bytes + 255) / 256 * 256; }
 void free_scratch(Scratch &s);
 
 // Brackets one kernel launch with HIP events when the plan profiles.
@@ -197,6 +202,18 @@ int residual_form(const fr_plan *pl);
 // the two trace arrays of the stage epilogue's ping-pong (allocated on first use)
 int stage_trace_buffers(fr_plan *pl, void *&a, void *&b);
 
+
+// The time steps' scratch.  rk: in single precision the accumulator (double),
+// the stage state and the residual; in double the stage states s4 (acc), s2 and
+// s3 (or the residual).  dual: the BDF constant and, in single precision, the
+// double copy of the stage velocities.
+struct RkBufs {
+    double *acc;
+    void *stT;
+    void *k;
+};
+int rk_buffers(fr_plan *pl, RkBufs &b);
+int dual_buffers(fr_plan *pl, double *&B, double *&st64);
 
 // Up to max_iters classical RK4 pseudo-steps of dU/dtau = R(U) - M_V (a U + B)
 // + D (D may be null) on plan pl, from U (double, in place).  The RMS of the

@@ -2286,9 +2286,19 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
                                  (pl->form == FR_FORM_AUTO && LinesShape<P, T>::AUTO == 1)));
     if (!MF && !sp && !DIAG && (pl->form == FR_FORM_LINES || pl->form == FR_FORM_HALO))
         return set_error(FR_EUNSUPPORTED, "line-task forms: diagonal Jacobians only");
+    // the line tasks and the stage epilogues load and store in 16 bytes
+    {
+        const void *const used[] = {U, R};
+        const void *const stage[] = {sp ? sp->U : nullptr, sp ? sp->acc : nullptr, sp ? sp->s_in : nullptr,
+                                     sp ? sp->s_out64 : nullptr, sp ? sp->s_out : nullptr,
+                                     sp ? sp->s2 : nullptr, sp ? sp->s3 : nullptr, sp ? sp->D : nullptr};
+        uintptr_t all = 0;
+        for (const void *q : used) all |= (uintptr_t)q;
+        for (const void *q : stage) all |= (uintptr_t)q;
+        if (all & 15) return set_error(FR_EINVAL, "fused residual: an array is not 16-byte aligned");
+    }
     if constexpr (!MF && !DIAG)
-        if (!sp && pl->form == FR_FORM_AUTO && pl->ne >= metric_least<P>() &&
-            (((uintptr_t)U | (uintptr_t)R) & 15) == 0) {
+        if (!sp && pl->form == FR_FORM_AUTO && pl->ne >= metric_least<P>()) {
             const Bricks g = bricks_for(MetricShape<P>::E, sizeof(T), pl->nx, pl->ny, pl->nz);
             ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
             hipLaunchKernelGGL((k_metric<P, T>), dim3((g.nb + 7) / 8 * 8), dim3(MetricShape<P>::NT), 0, s, U, R,

@@ -171,11 +171,9 @@ int pseudo_residual(fr_plan *pl, const double *U, const double *B, const double 
     const int64_t n = (int64_t)fr_state_len(pl);
     const int ns = pl->m * pl->m * pl->m;
     const bool f64 = pl->precision == FR_F64;
-    const size_t esz = f64 ? 8 : 4;
-    // the plan's RK scratch: [acc (double)][stage (T)][k (T)]
-    if (int rc = ensure_scratch(pl->rk, (size_t)n * 8 + 2 * (size_t)n * esz)) return rc;
-    void *st = (char *)pl->rk.ptr + n * 8;
-    void *k = (char *)st + n * esz;
+    RkBufs b;
+    if (int rc = rk_buffers(pl, b)) return rc;
+    void *st = b.stT, *k = b.k;
     if (!f64)
         if (int rc = launch_to_precision(pl, U, st, n, s)) return rc;
     const int rc = launch_residual(pl, f64 ? (const void *)U : st, k, s);
