@@ -60,7 +60,7 @@ bool stage_in_epilogue(const fr_plan *pl)
 uint64_t config_word(const fr_plan *pl)
 {
     return (uint64_t)pl->precision | (uint64_t)pl->variant << 8 | (uint64_t)pl->fuse_stage << 16 |
-           (uint64_t)pl->pseudo << 24 | (uint64_t)(uint32_t)pl->block << 32;
+           (uint64_t)pl->pseudo << 24 | (uint64_t)(uint32_t)pl->block << 32 | (uint64_t)pl->form << 48;
 }
 
 uint64_t bits(double x)
