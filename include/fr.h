@@ -57,7 +57,8 @@ typedef enum fr_status {
 typedef enum fr_option {
     FR_OPT_PRECISION = 1, /* FR_F64 (default) or FR_F32: working precision of the residual */
     FR_OPT_VARIANT = 2,   /* FR_FUSED (default), FR_UNFUSED or FR_MFMA (see fr_residual)   */
-    FR_OPT_BLOCK = 3,     /* elements per workgroup of the fused kernel; 0 = tuned default  */
+    FR_OPT_BLOCK = 3,     /* elements per workgroup of the fused (point form's) kernel; 0 =
+                             tuned default.  The line and halo forms have their own        */
     FR_OPT_PROFILE = 4,   /* 1: record HIP events around every kernel launch (see below)   */
     FR_OPT_GUESS_BASE = 5,/* extrapolation the learned guess corrects: 2 quadratic (default),
                              1 linear                                                      */
@@ -99,7 +100,8 @@ typedef enum fr_option {
                              of FR_FORM_LINES; FR_FORM_AUTO (default) the fastest measured:
                              the halo form with a diagonal Jacobian, else the point form, for
                              whose residual larger lattices take one kernel of line tasks in
-                             which each lane forms its neighbours' traces (equal to rounding).
+                             which each lane forms its neighbours' traces (equal to rounding),
+                             unless FR_OPT_BLOCK is set.
                              The point and line forms agree to rounding (not bitwise); the
                              stage epilogue of fr_rk_step /
                              fr_dual_step uses the halo form's kernel when that is the

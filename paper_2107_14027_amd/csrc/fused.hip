@@ -2234,7 +2234,8 @@ __global__ void __launch_bounds__(MetricShape<P>::NT)
 // FR_FORM_AUTO's smallest lattice of a general Jacobian on k_metric: from 4^3 the
 // one launch is ahead (p = 1..4 FP64 9 to 15 us, the two of the point form 18 to
 // 21); from p = 5 on it is even with them up to 8^3 (p = 6 FP64 27.5 and 26.5 us)
-// and ahead from 12^3 (68 and 82).
+// and ahead from 12^3 (68 and 82).  (FR_OPT_BLOCK is a setting of the point form's
+// kernel, which runs where it is set.)
 template <int P> constexpr int64_t metric_least() { return P >= 5 ? 1000 : 64; }
 
 // ---------------------------------------------------------------------------
@@ -2298,7 +2299,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
         if (all & 15) return set_error(FR_EINVAL, "fused residual: an array is not 16-byte aligned");
     }
     if constexpr (!MF && !DIAG)
-        if (!sp && pl->form == FR_FORM_AUTO && pl->ne >= metric_least<P>()) {
+        if (!sp && pl->form == FR_FORM_AUTO && !pl->block && pl->ne >= metric_least<P>()) {
             const Bricks g = bricks_for(MetricShape<P>::E, sizeof(T), pl->nx, pl->ny, pl->nz);
             ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
             hipLaunchKernelGGL((k_metric<P, T>), dim3((g.nb + 7) / 8 * 8), dim3(MetricShape<P>::NT), 0, s, U, R,
