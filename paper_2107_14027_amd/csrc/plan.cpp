@@ -364,7 +364,6 @@ int fr_plan_set_int(fr_plan *pl, int key, int value)
             if (value != pl->precision) {
                 hipDeviceSynchronize();
                 free_scratch(pl->traces);
-    free_scratch(pl->traces2);
                 free_scratch(pl->traces2);
                 free_scratch(pl->unfused);
                 free_scratch(pl->rk);
@@ -453,6 +452,7 @@ void fr_plan_destroy(fr_plan *pl)
     graphs_reset(pl);
     if (pl->cap_stream) hipStreamDestroy(pl->cap_stream);
     free_scratch(pl->traces);
+    free_scratch(pl->traces2);
     free_scratch(pl->unfused);
     free_scratch(pl->rk);
     free_scratch(pl->dual);
