@@ -188,7 +188,8 @@ size_t fr_state_len(const fr_plan *plan);
  * followed by its two common interface values, in single-precision operands
  * with single-precision accumulation (v_mfma_f32_16x16x4f32).  It requires
  * FR_F32 (FR_EUNSUPPORTED in FR_F64); fr_rk_step and fr_dual_step then use the
- * separate stage kernel.  Allocates the plan's trace scratch on first use.
+ * separate stage kernel.  Allocates the plan's trace scratch on first use in a
+ * form that keeps face traces in memory.
  */
 int fr_residual(fr_plan *plan, const void *U, void *R, fr_stream_t s);
 

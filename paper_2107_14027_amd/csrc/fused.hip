@@ -2236,7 +2236,11 @@ __global__ void __launch_bounds__(MetricShape<P>::NT)
 // 21); from p = 5 on it is even with them up to 8^3 (p = 6 FP64 27.5 and 26.5 us)
 // and ahead from 12^3 (68 and 82).  (FR_OPT_BLOCK is a setting of the point form's
 // kernel, which runs where it is set.)
-template <int P> constexpr int64_t metric_least() { return P >= 5 ? 1000 : 64; }
+bool metric_takes(const fr_plan *pl)
+{
+    return pl->variant == FR_FUSED && !pl->c64.diag && pl->form == FR_FORM_AUTO && !pl->block &&
+           pl->ne >= (pl->p >= 5 ? 1000 : 64);
+}
 
 // ---------------------------------------------------------------------------
 // launch
@@ -2299,7 +2303,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
         if (all & 15) return set_error(FR_EINVAL, "fused residual: an array is not 16-byte aligned");
     }
     if constexpr (!MF && !DIAG)
-        if (!sp && pl->form == FR_FORM_AUTO && !pl->block && pl->ne >= metric_least<P>()) {
+        if (!sp && metric_takes(pl)) {
             const Bricks g = bricks_for(MetricShape<P>::E, sizeof(T), pl->nx, pl->ny, pl->nz);
             ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
             hipLaunchKernelGGL((k_metric<P, T>), dim3((g.nb + 7) / 8 * 8), dim3(MetricShape<P>::NT), 0, s, U, R,
@@ -2447,10 +2451,11 @@ size_t trace_bytes(const fr_plan *pl)
 int fused_any(fr_plan *pl, const void *U, void *R, const StageSpec *sp, int *nparts,
               hipStream_t s, void *TR = nullptr, bool prof = true, bool mf = false)
 {
-    // the halo form needs no trace array (for a stage, the stage path decides
-    // the form: the point form's epilogue may follow a halo-form residual)
-    const bool halo = !mf && (sp ? stage_path(pl) == FR_STAGE_HALO : residual_form(pl) == FR_FORM_HALO);
-    if (!TR && !halo) {
+    // the halo form and k_metric need no trace array (for a stage, the stage path
+    // decides the form: the point form's epilogue may follow their residuals)
+    const bool none = !mf && (sp ? stage_path(pl) == FR_STAGE_HALO
+                                 : residual_form(pl) == FR_FORM_HALO || metric_takes(pl));
+    if (!TR && !none) {
         if (int rc = ensure_scratch(pl->traces, trace_bytes(pl))) return rc;
         TR = pl->traces.ptr;
     }

@@ -37,3 +37,20 @@ def test_destroy_gives_everything_back():
         plan.close()
         free_after.append(free())
     assert free_after[0] - free_after[2] < TRACES // 2
+
+
+@pytest.mark.parametrize("form,arrays", [(B.FR_FORM_AUTO, 0), (B.FR_FORM_POINT, 1)])
+def test_residual_of_a_general_jacobian_takes_what_it_reads(form, arrays):
+    """The automatic form's one kernel has no face traces in memory."""
+    import torch
+    say("residual memory form=%d" % form)
+    U = state()
+    R = torch.empty_like(U)
+    for _ in range(2):      # the first time pays for what the library itself keeps
+        plan = B.Plan(P, N, ZETA, NU, T_CFG, SKEW)
+        plan.set(B.FR_OPT_FORM, form)
+        start = free()
+        B.fr_residual(plan.handle, U, R)
+        used = start - free()
+        plan.close()
+    assert arrays * TRACES <= used < arrays * TRACES + TRACES // 2
