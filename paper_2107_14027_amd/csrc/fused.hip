@@ -471,20 +471,6 @@ template <int P, bool DIAG> struct LineDiv {
     static constexpr bool value = DIAG && P >= FR_LDIV_PMIN;
 };
 
-// Values per thread whose global operands the stage epilogue requests at once,
-// per order and precision (a larger chunk overlaps more loads but can cost a
-// wave of occupancy; measured).  FR_STG_CHUNK overrides the table.
-template <int P, typename T, bool DIAG>
-constexpr int stage_chunk()
-{
-#ifdef FR_STG_CHUNK
-    return FR_STG_CHUNK;
-#else
-    constexpr int d[PMAX + 1] = {0, 6, 6, 8, 4, 6, 6};
-    return sizeof(T) == 4 || (P == 5 && !DIAG) ? 4 : d[P];
-#endif
-}
-
 // Global loads and stores of the stage update, marked nontemporal (NTS) where
 // that measured faster: in the halo form's epilogue for states that the caches
 // cannot hold (STAGE_KEEP_BYTES), in the point form's except at p = 4 (where it
@@ -510,17 +496,35 @@ __device__ __forceinline__ void stg_st(X *p, X v)
 struct StageOps {
     double u, acc, s2, s3, s, b, d;
 };
+enum { STG_PLAIN = 0, STG_BDF = 1, STG_BDF_FIXED = 2 };   // the sources: none, B, B and D
+
+// Values per thread whose global operands the point form's stage epilogue requests
+// at once, per order, precision and use (a larger chunk overlaps more loads, until
+// its registers cost a wave of occupancy).  Measured on RK4 and dual steps on 4^3,
+// 12^3 and 24^3 hexes with a general Jacobian and 4^3, 16^3 with a diagonal one,
+// against one loop that decided stage and sources per value: RK4 steps 0.97 (p = 3
+// in single precision on 4^3) to 1.32 times as fast (p = 1 in double on 16^3), dual
+// steps 0.99 to 1.42.
+template <int P, typename T, bool DIAG, bool LAST, int SRC>
+constexpr int stage_chunk()
+{
+    constexpr int d[PMAX + 1] = {0, 7, 8, 7, 5, LAST ? 3 : 6, 6};
+    constexpr int plain[PMAX + 1] = {0, 13, LAST ? 11 : 6, DIAG ? 4 : 5, 5, LAST ? 8 : 4, 6};
+    constexpr int bdf[PMAX + 1] = {0, 8, 4, DIAG ? 4 : 5, 3, 4, 6};
+    return sizeof(T) == 8 ? d[P] : (SRC == STG_PLAIN ? plain[P] : bdf[P]);
+}
 
 // The RK stage update of one value from its residual kv, in the double
 // arithmetic of the stand-alone stage kernels: the next stage state or, on the
 // last stage, the new U; in single precision also the new accumulator.  vel: a
-// velocity value; ss accumulates its squared pseudo-residual.
-template <typename T>
+// velocity value; ss accumulates its squared pseudo-residual.  SRC negative: the
+// sources are decided here.
+template <typename T, int SRC = -1>
 __device__ __forceinline__ double stage_value(const StageSpec &sp, bool last, double kv, bool vel,
                                               const StageOps &o, double &acc, double &ss)
 {
-    if (vel && sp.B) kv -= fma(sp.a, o.s, o.b);
-    if (sp.D) kv += o.d;
+    if (vel && (SRC < 0 ? sp.B != nullptr : SRC != STG_PLAIN)) kv -= fma(sp.a, o.s, o.b);
+    if (SRC < 0 ? sp.D != nullptr : SRC == STG_BDF_FIXED) kv += o.d;
     if (vel && sp.partial) ss = fma(kv, kv, ss);
     if constexpr (sizeof(T) == 8) {
         if (last) return rk4_last(o.u, fma(2.0, o.s3 - o.u, o.s2 - o.u), o.s, sp.b, kv);
@@ -547,13 +551,15 @@ __device__ __forceinline__ bool stage_reads_acc(const StageSpec &sp)
 // chunk are requested before the first is used, so that the loads of a wave
 // overlap, with a bounded register cost.  With tr_out the produced state
 // replaces the residual in the tile.
-// (LAST and the two uses of the BDF source are told apart outside the loops:
-// decided per value they cost 15-30 % of a stage.)
-template <int J, int C, int NS, typename T, bool NTS, bool LAST, bool BDF, typename Tile>
+// (LAST and SRC are told apart outside the loops: decided per value they cost 15-30 %
+// of a stage, the fixed source alone 16 % of a general Jacobian's dual step at p = 3,
+// 24^3 in double.)
+template <int J, int C, int NS, typename T, bool NTS, bool LAST, int SRC, typename Tile>
 __device__ __forceinline__ void stage_update_as(const StageSpec &sp, Tile &&tile, unsigned tid,
                                                 unsigned nt, unsigned cnt, int64_t e0, double &ss)
 {
     constexpr bool D64 = sizeof(T) == 8;
+    constexpr bool BDF = SRC != STG_PLAIN, FIXED = SRC == STG_BDF_FIXED;
     const int64_t g0 = e0 * NV * NS;
     const double *sin = sp.s_in ? sp.s_in : sp.U;
 #pragma unroll 1
@@ -566,20 +572,20 @@ __device__ __forceinline__ void stage_update_as(const StageSpec &sp, Tile &&tile
                 const int64_t gi = g0 + t;
                 if (D64 || !LAST || sp.first) o[j].u = stg_ld<NTS>(sp.U + gi);
                 if (stage_reads_acc<T>(sp)) o[j].acc = stg_ld<NTS>(sp.acc + gi);
-                if constexpr (D64 && LAST) {
+                if (D64 && LAST) {
                     o[j].s2 = stg_ld<NTS>(sp.s2 + gi);
                     o[j].s3 = stg_ld<NTS>(sp.s3 + gi);
                     o[j].s = stg_ld<NTS>(sin + gi);
                 }
-                if constexpr (BDF) {
+                if (BDF) {
                     const unsigned r = t / NS, q = t - r * NS;
                     const unsigned el = r / NV, v = r - el * NV;
                     if (v >= 1 && v <= 3) {
-                        if (!(D64 && LAST)) o[j].s = stg_ld<NTS>(sin + gi);
-                        o[j].b = stg_ld<NTS>(sp.B + ((int64_t)(e0 + el) * 3 + (v - 1)) * NS + q);
+                        if (!(D64 && LAST)) o[j].s = sin[gi];
+                        o[j].b = sp.B[((int64_t)(e0 + el) * 3 + (v - 1)) * NS + q];
                     }
                 }
-                if (sp.D) o[j].d = stg_ld<NTS>(sp.D + gi);
+                if (FIXED) o[j].d = stg_ld<NTS>(sp.D + gi);
             }
         }
 #pragma unroll
@@ -590,27 +596,37 @@ __device__ __forceinline__ void stage_update_as(const StageSpec &sp, Tile &&tile
                 const unsigned v = (t / NS) % NV;
                 const bool vel = v >= 1 && v <= 3;
                 double acc;
-                const double next = stage_value<T>(sp, LAST, (double)tile(t), vel, o[j], acc, ss);
-                if (LAST) stg_st<NTS>(sp.U + gi, next);
-                else if (!D64) stg_st<NTS>(sp.acc + gi, acc);
-                if (BDF && sp.s_out64 && vel) stg_st<NTS>(sp.s_out64 + gi, next);
-                if (sp.s_out) stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)next);
+                const double next = stage_value<T, SRC>(sp, LAST, (double)tile(t), vel, o[j], acc, ss);
+                if (LAST) {
+                    stg_st<NTS>(sp.U + gi, next);
+                    if (sp.s_out) stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)next);
+                } else {
+                    if (!D64) stg_st<NTS>(sp.acc + gi, acc);
+                    if (BDF && sp.s_out64 && vel) stg_st<NTS>(sp.s_out64 + gi, next);
+                    stg_st<NTS>(static_cast<T *>(sp.s_out) + gi, (T)next);
+                }
                 if (sp.tr_out) tile(t) = (T)next;
             }
         }
     }
 }
-template <int J, int C, int NS, typename T, bool NTS, typename Tile>
+template <int P, int J, typename T, bool DIAG, bool NTS, typename Tile>
 __device__ __forceinline__ void stage_update_batch(const StageSpec &sp, Tile &&tile, unsigned tid,
                                                    unsigned nt, unsigned cnt, int64_t e0, double &ss)
 {
-    if (sp.last) {
-        if (sp.B) stage_update_as<J, C, NS, T, NTS, true, true>(sp, tile, tid, nt, cnt, e0, ss);
-        else stage_update_as<J, C, NS, T, NTS, true, false>(sp, tile, tid, nt, cnt, e0, ss);
-    } else {
-        if (sp.B) stage_update_as<J, C, NS, T, NTS, false, true>(sp, tile, tid, nt, cnt, e0, ss);
-        else stage_update_as<J, C, NS, T, NTS, false, false>(sp, tile, tid, nt, cnt, e0, ss);
-    }
+    constexpr int NS = (P + 1) * (P + 1) * (P + 1);
+    auto as = [&](auto last, auto src) {
+        constexpr bool LAST = decltype(last)::value != 0;
+        constexpr int SRC = decltype(src)::value, c = stage_chunk<P, T, DIAG, LAST, SRC>(), C = c < J ? c : J;
+        stage_update_as<J, C, NS, T, NTS, LAST, SRC>(sp, tile, tid, nt, cnt, e0, ss);
+    };
+    auto source = [&](auto last) {
+        if (sp.D) as(last, Dir<STG_BDF_FIXED>{});
+        else if (sp.B) as(last, Dir<STG_BDF>{});
+        else as(last, Dir<STG_PLAIN>{});
+    };
+    if (sp.last) source(Dir<1>{});
+    else source(Dir<0>{});
 }
 
 // Pairs of consecutive values of an element, v0 and v0 + 1, in one 16-byte
@@ -1205,10 +1221,9 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
             //      are requested before the first is used, so that the loads of a
             //      wave overlap, with a bounded register cost.
             constexpr int J = (EMAX * NV * NS + NT - 1) / NT;
-            constexpr int C = stage_chunk<P, T, DIAG>() < J ? stage_chunk<P, T, DIAG>() : J;
             __syncthreads();
-            stage_update_batch<J, C, NS, T, P != 4>(sp, [&](unsigned t) -> T & { return sU[t]; }, tid, NT,
-                                           (unsigned)nel * NV * NS, e0, ss);
+            stage_update_batch<P, J, T, DIAG, P != 4>(sp, [&](unsigned t) -> T & { return sU[t]; }, tid, NT,
+                                                      (unsigned)nel * NV * NS, e0, ss);
             if (sp.tr_out) {
                 // ---- stage 1 of the next residual: the produced state's face
                 //      traces (k_trace's values and layout) from the tile, written
@@ -2275,6 +2290,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
                              (pl->form == FR_FORM_AUTO && LinesShape<P, T>::AUTO == 2)));
     if (sp && !STG_OK && !halo)
         return set_error(FR_EUNSUPPORTED, "stage epilogue not available at p=%d", P);
+    if (sp && sp->D && !sp->B) return set_error(FR_EINVAL, "stage epilogue: a fixed source without the BDF term");
     if (sp && halo && (sp->tr_in || sp->tr_out))
         return set_error(FR_EINVAL, "halo-form stage epilogue: no face-trace arrays");
     const void *kfu = (const void *)k_fused<P, T, DIAG, false>;
