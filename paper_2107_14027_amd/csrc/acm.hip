@@ -631,6 +631,7 @@ struct fr_acm {
     fr::AcmArgs args;
     double *utr = nullptr, *Q = nullptr, *FI = nullptr;
     double *ops = nullptr;   // operators of k_acm_lines
+    fr::dev::Bricks bricks;
     // dual time stepping (allocated on its first call): residual, stage state,
     // RK accumulator, BDF constant, norm partials and result, pinned read-back
     double *R = nullptr, *S = nullptr, *acc = nullptr, *B = nullptr, *part = nullptr;
@@ -705,9 +706,22 @@ bool lines_take(const fr_acm *a, const double *U, const double *R)
 }
 
 template <int M>
+int set_bricks(fr_acm *a)
+{
+    a->bricks = bricks_for(AcmLineShape<M - 1>::E, 8, a->args.nx, a->args.ny, a->args.nz);
+    return FR_OK;
+}
+int lines_bricks(fr_acm *a)
+{
+#define FR_ACM_BRICKS(M) set_bricks<M>(a)
+    FR_ACM_ORDERS(FR_ACM_BRICKS)
+#undef FR_ACM_BRICKS
+}
+
+template <int M>
 int launch_lines(fr_acm *a, const double *U, double *R, hipStream_t s)
 {
-    const Bricks g = bricks_for(AcmLineShape<M - 1>::E, 8, a->args.nx, a->args.ny, a->args.nz);
+    const Bricks &g = a->bricks;
     hipLaunchKernelGGL(k_acm_lines<M - 1>, dim3((g.nb + 7) / 8 * 8), dim3(192), 0, s, U, R, a->ops, a->args, g);
     return check_hip(hipGetLastError(), "k_acm_lines launch");
 }
@@ -809,6 +823,10 @@ fr_acm *fr_acm_create(fr_plan *plan, double ldg_beta, double ldg_tau)
     A.nu = plan->nu;
     A.beta = ldg_beta;
     A.tau = ldg_tau;
+    if (lines_bricks(a)) {
+        fr_acm_destroy(a);
+        return nullptr;
+    }
     const int64_t ne = plan->ne;
     const size_t nfp = (size_t)m * m, ns = nfp * m;
     if (check_hip(hipMalloc((void **)&a->utr, (size_t)ne * 6 * NA * nfp * sizeof(double)), "hipMalloc(acm traces)") ||

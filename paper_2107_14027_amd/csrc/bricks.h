@@ -134,27 +134,6 @@ __device__ __forceinline__ int lt_base(int L)
 // elements (at most LinesShape::E), neighbours of each other in the lattice, so
 // that the faces between them are formed from the tile; bricks at the lattice's
 // upper ends may stick out of it (those slots idle).
-//
-// Division of n < 2^31 by a number fixed on the host: n / d = n m >> s with
-// 2^(s - 32) < d <= 2^(s - 31), m = ceil(2^s / d) (the excess of m d over 2^s is
-// below 2^(s - 31), too little to reach the next quotient).
-struct FastDiv {
-    uint32_t m;
-    int s;
-    __device__ __forceinline__ unsigned operator()(unsigned n) const
-    {
-        return (unsigned)(((uint64_t)n * m) >> s);
-    }
-};
-struct Bricks {
-    int bx, by, bz;        // elements of a brick along x, y, z
-    int mx, mxy;           // ceil(2^16 / bx), ceil(2^16 / (bx by)): n / bx = n mx >> 16 for n < 256
-    int gx, gy;            // bricks of the lattice along x, y
-    FastDiv by_gx, by_gy;
-    unsigned nb;           // bricks of the lattice
-    unsigned chunk;        // bricks of an XCD's share of a group (brick_of)
-    FastDiv by_group;      // by 8 chunk
-};
 
 // Elements of the brick (slot coordinates sx, sy, sz, lattice element e; e < 0:
 // slot not in use).
@@ -346,6 +325,8 @@ __device__ __forceinline__ void slot_store(const T *slot, int lo, T *__restrict_
 // one-element bricks and one of up to E times that smaller ones in proportion:
 // such a call takes one workgroup's latency, which grows with its brick (RK4 step
 // at p = 3 in double on 6^3 hexes: 44 us with one-element bricks, 56 with four).
+// Plans and objects keep theirs: up to 0.4 us a launch on the host otherwise (p = 1,
+// 16^3: 8.7 us a residual, 8.9 when every call worked them out).
 inline dev::FastDiv fast_div(uint32_t d)
 {
     dev::FastDiv f{0, 31};

@@ -37,6 +37,30 @@ struct OpsLayout {
     static constexpr int x = size;   // the solution points, behind the operators
 };
 
+// The bricks of elements a lattice is cut into for one kernel (bricks.h).
+namespace dev {
+// Division of n < 2^31 by a number fixed on the host: n / d = n m >> s with
+// 2^(s - 32) < d <= 2^(s - 31), m = ceil(2^s / d) (the excess of m d over 2^s is
+// below 2^(s - 31), too little to reach the next quotient).
+struct FastDiv {
+    uint32_t m;
+    int s;
+    __device__ __forceinline__ unsigned operator()(unsigned n) const
+    {
+        return (unsigned)(((uint64_t)n * m) >> s);
+    }
+};
+struct Bricks {
+    int bx, by, bz;        // elements of a brick along x, y, z
+    int mx, mxy;           // ceil(2^16 / bx), ceil(2^16 / (bx by)): n / bx = n mx >> 16 for n < 256
+    int gx, gy;            // bricks of the lattice along x, y
+    FastDiv by_gx, by_gy;
+    unsigned nb;           // bricks of the lattice
+    unsigned chunk;        // bricks of an XCD's share of a group (brick_of)
+    FastDiv by_group;      // by 8 chunk
+};
+}  // namespace dev
+
 struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
@@ -126,6 +150,8 @@ struct fr_plan {
     // 1 once the LDS limit of the unfused stage-1 kernel is set (order, precision)
     int unfused_attr[fr::PMAX + 1][2] = {};
     int device;
+    // bricks of the line forms and of k_metric, per precision
+    fr::dev::Bricks lines_bricks[2], metric_bricks[2];
     // host copies of the operators (double)
     double x[8], w[8], D[64], lm[8], lp[8], gl[8], gr[8], Dt[64];
     // device operator blocks
@@ -193,6 +219,8 @@ int launch_residual_stage(fr_plan *pl, const void *U, const StageSpec &sp, int *
 // How fr_rk_step / fr_dual_step apply the RK stage update for this plan's
 // current settings (FR_STAGE_SEPARATE, FR_STAGE_POINT or FR_STAGE_HALO).
 int stage_path(const fr_plan *pl);
+// Works out lines_bricks and metric_bricks.
+void plan_bricks(fr_plan *pl);
 // Partial norm sums the stage-epilogue launch of this plan writes at most (the
 // halo form's: one per batch; 0 for the other paths).
 int stage_partials(const fr_plan *pl);

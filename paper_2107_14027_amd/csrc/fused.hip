@@ -2320,7 +2320,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
     }
     if constexpr (!MF && !DIAG)
         if (!sp && metric_takes(pl)) {
-            const Bricks g = bricks_for(MetricShape<P>::E, sizeof(T), pl->nx, pl->ny, pl->nz);
+            const Bricks &g = pl->metric_bricks[sizeof(T) == 8 ? FR_F64 : FR_F32];
             ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
             hipLaunchKernelGGL((k_metric<P, T>), dim3((g.nb + 7) / 8 * 8), dim3(MetricShape<P>::NT), 0, s, U, R,
                                ops, c, pl->nx, pl->ny, pl->nz, g);
@@ -2386,7 +2386,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
         // (what a launch may ask for without hipFuncSetAttribute: six calls of it
         // were a good part of a plan's first residual on a small lattice)
         static_assert(lds_li <= 64 * 1024, "LDS");
-        const Bricks g = bricks_for(LE, sizeof(T), pl->nx, pl->ny, pl->nz);
+        const Bricks &g = pl->lines_bricks[sizeof(T) == 8 ? FR_F64 : FR_F32];
         const unsigned blocks = (g.nb + 7) / 8 * 8;
         ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
         if constexpr (DIAG) {
@@ -2613,24 +2613,29 @@ int stage_path(const fr_plan *pl)
     return pl->ne <= m ? point : FR_STAGE_HALO;
 }
 
-int stage_partials(const fr_plan *pl)
+void plan_bricks(fr_plan *pl)
 {
-    if (stage_path(pl) != FR_STAGE_HALO) return 0;
-    const bool f64 = pl->precision == FR_F64;
-    auto pick = [&](auto pc) {
+    auto set = [&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        const int E = f64 ? LinesShape<P, double>::E : LinesShape<P, float>::E;
-        return (int)bricks_for(E, f64 ? 8 : 4, pl->nx, pl->ny, pl->nz).nb;
+        const int nx = pl->nx, ny = pl->ny, nz = pl->nz;
+        pl->lines_bricks[FR_F64] = bricks_for(LinesShape<P, double>::E, 8, nx, ny, nz);
+        pl->lines_bricks[FR_F32] = bricks_for(LinesShape<P, float>::E, 4, nx, ny, nz);
+        pl->metric_bricks[FR_F64] = bricks_for(MetricShape<P>::E, 8, nx, ny, nz);
+        pl->metric_bricks[FR_F32] = bricks_for(MetricShape<P>::E, 4, nx, ny, nz);
     };
     switch (pl->p) {
-        case 1: return pick(Dir<1>{});
-        case 2: return pick(Dir<2>{});
-        case 3: return pick(Dir<3>{});
-        case 4: return pick(Dir<4>{});
-        case 5: return pick(Dir<5>{});
-        case 6: return pick(Dir<6>{});
+        case 1: set(Dir<1>{}); break;
+        case 2: set(Dir<2>{}); break;
+        case 3: set(Dir<3>{}); break;
+        case 4: set(Dir<4>{}); break;
+        case 5: set(Dir<5>{}); break;
+        case 6: set(Dir<6>{}); break;
     }
-    return 0;
+}
+
+int stage_partials(const fr_plan *pl)
+{
+    return stage_path(pl) == FR_STAGE_HALO ? (int)pl->lines_bricks[pl->precision].nb : 0;
 }
 
 int launch_residual_stage(fr_plan *pl, const void *U, const StageSpec &sp, int *nparts,

@@ -352,7 +352,7 @@ template <int M>
 int launch_lhex(fr_lhex *h, const double *corners, const double *U, double *R, hipStream_t s)
 {
     if ((((uintptr_t)U | (uintptr_t)R) & 15) == 0) {
-        const dev::Bricks g = bricks_for(dev::MetricShape<M - 1>::E, 8, h->args.nx, h->args.ny, h->args.nz);
+        const dev::Bricks &g = h->plan->metric_bricks[FR_F64];
         hipLaunchKernelGGL(k_lh_lines<M - 1>, dim3((g.nb + 7) / 8 * 8), dim3(dev::MetricShape<M - 1>::NT),
                            0, s, corners, U, R, (const double *)h->plan->ops64, h->args.zeta, h->args.nu, h->args.invT,
                            h->args.nx, h->args.ny, h->args.nz, g);

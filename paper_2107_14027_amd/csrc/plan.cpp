@@ -326,6 +326,7 @@ fr_plan *fr_plan_create(int p, int nx, int ny, int nz, const double jac[9], doub
     std::memcpy(pl->Dt, o.Dt, sizeof o.Dt);
     fill_consts(pl, pl->c64);
     fill_consts(pl, pl->c32);
+    fr::plan_bricks(pl);
 
     if (check_hip(hipGetDevice(&pl->device), "hipGetDevice") || fr::scratch_setup(pl->device)) {
         delete pl;
