@@ -325,6 +325,10 @@ __device__ __forceinline__ void slot_store(const T *slot, int lo, T *__restrict_
 // one-element bricks and one of up to E times that smaller ones in proportion:
 // such a call takes one workgroup's latency, which grows with its brick (RK4 step
 // at p = 3 in double on 6^3 hexes: 44 us with one-element bricks, 56 with four).
+// One with more bricks than that, but not more than two for each CU, gets the
+// smallest ones that stay within two, if they are smaller by a tenth (p = 2 in double
+// on 12^3 hexes: 432 bricks of four 8.5 us a residual and 46 an RK4 step, 288 of six
+// 9.0 and 53).
 // Plans and objects keep theirs: up to 0.4 us a launch on the host otherwise (p = 1,
 // 16^3: 8.7 us a residual, 8.9 when every call worked them out).
 inline dev::FastDiv fast_div(uint32_t d)
@@ -341,16 +345,35 @@ inline dev::Bricks bricks_for(int E, int esize, int nx, int ny, int nz)
     const int few = esize == 8 ? 256 : 512;
     const int most = (int)std::min<int64_t>(E, (ne + few - 1) / few);
     dev::Bricks g{};
-    double best = 0.0;
-    for (int bx = most; bx >= 1; --bx)
-        for (int by = 1; bx * by <= most; ++by)
-            for (int bz = 1; bx * by * bz <= most; ++bz) {
-                const double nb = (double)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
-                const double cost = nb * (4 * E + bx * by + by * bz + bz * bx);
-                if (g.bx && cost >= best) continue;
-                best = cost;
-                g.bx = bx, g.by = by, g.bz = bz;
-            }
+    auto bricks = [&](int bx, int by, int bz) {
+        return (double)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
+    };
+    auto choose = [&](auto &&cost) {
+        double best = 0.0;
+        bool any = false;
+        for (int bx = most; bx >= 1; --bx)
+            for (int by = 1; bx * by <= most; ++by)
+                for (int bz = 1; bx * by * bz <= most; ++bz) {
+                    const double c = cost(bx, by, bz);
+                    if (any && c >= best) continue;
+                    any = true;
+                    best = c;
+                    g.bx = bx, g.by = by, g.bz = bz;
+                }
+    };
+    auto throughput = [&](int bx, int by, int bz) {
+        return bricks(bx, by, bz) * (4 * E + bx * by + by * bz + bz * bx);
+    };
+    choose(throughput);
+    const double nb = bricks(g.bx, g.by, g.bz);
+    if (nb > few && nb <= 2 * few) {
+        const dev::Bricks large = g;
+        choose([&](int bx, int by, int bz) {
+            const double n = bricks(bx, by, bz), t = 1e-15 * throughput(bx, by, bz);
+            return n > 2 * few ? 1e9 + t : (n > few ? 2 : 1) * (bx * by * bz) + t;
+        });
+        if (10 * g.bx * g.by * g.bz > 9 * large.bx * large.by * large.bz) g = large;
+    }
     g.mx = (65536 + g.bx - 1) / g.bx;
     g.mxy = (65536 + g.bx * g.by - 1) / (g.bx * g.by);
     g.gx = (nx + g.bx - 1) / g.bx;
