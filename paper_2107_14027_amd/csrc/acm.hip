@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(RES_TB) k_acm_resid(const double *__restrict__
 // in the order x, y, z over the tile, which is then R.
 //
 // Floor: 8 values per point (0.22 ms at the rate of a copy for p = 4 on 51^3
-// hexes, 16.6 M points): 0.50 ms there, with 148 VGPRs, 12 waves per CU and the 24
+// hexes, 16.6 M points): 0.50 ms there, with 146 VGPRs, 12 waves per CU and the 24
 // neighbour values per point out of the caches; the four kernels above, 66 values
 // per point through memory, take 3.3 ms.
 // ---------------------------------------------------------------------------
@@ -305,22 +305,29 @@ __device__ __forceinline__ double dot(const double *__restrict__ w, const double
 }
 
 // Common flux through a face of direction D between L (minus side) and R, with
-// the common viscous flux fv along e_D, times the face scaling.  The unit normal
-// is e_D or, with a negative Jacobian entry, -e_D: what is linear in it takes the
-// signed n_D, the jump terms its length.
-template <int D>
+// the common viscous flux fv.n, times the face scaling.  The unit normal is e_D or,
+// with a negative Jacobian entry, -e_D: what is linear in it takes its sign.  SPLIT:
+// of P the jump term alone, the central part is zeta n_D vm, vm the mean velocity
+// along e_D.
+template <int D, bool SPLIT>
 __device__ __forceinline__ void acm_face(const double (&L)[NA], const double (&R)[NA],
-                                         const double (&fv)[3], const AcmArgs &A, double (&out)[NA])
+                                         const double (&fv)[3], const AcmArgs &A, double (&out)[NA],
+                                         double &vm)
 {
-    const double vL = L[1 + D], vR = R[1 + D], n = A.nmag[D], ns = A.nvec[4 * D];
+    const double vL = L[1 + D], vR = R[1 + D], n = A.nmag[D], half = signed_nu(0.5, A.nvec[4 * D]);
     const double lam = fmax(fabs(vL) + sqrt(fma(vL, vL, A.zeta)), fabs(vR) + sqrt(fma(vR, vR, A.zeta)));
-    out[0] = ns * (0.5 * A.zeta * (vL + vR)) - n * (0.5 * lam * (R[0] - L[0]));
+    if constexpr (SPLIT) {
+        out[0] = -n * (0.5 * lam * (R[0] - L[0]));
+        vm = 0.5 * (vL + vR);
+    } else {
+        out[0] = n * (half * A.zeta * (vL + vR) - 0.5 * lam * (R[0] - L[0]));
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         double mL = L[1 + c] * vL, mR = R[1 + c] * vR;
         if (c == D) mL += L[0], mR += R[0];
-        out[1 + c] = ns * (0.5 * (mL + mR) + fv[c]) -
-                     n * (0.5 * lam * (R[1 + c] - L[1 + c]) - A.tau * (L[1 + c] - R[1 + c]));
+        out[1 + c] = n * (half * (mL + mR) - 0.5 * lam * (R[1 + c] - L[1 + c]) + fv[c] +
+                          A.tau * (L[1 + c] - R[1 + c]));
     }
 }
 
@@ -355,12 +362,19 @@ __device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const do
 {
     constexpr int M = P + 1, NS = M * M * M, STR = D == 0 ? 1 : (D == 1 ? M : M * M);
     using OL = AcmOps<M>;
+    // P's part as zeta n_D times the velocity's corrected derivative and the jump
+    // terms apart: with zeta n_D vm in the faces' flux, rounded before g_L and g_R
+    // scale it, P was up to 10 % further from the exact value than with the four
+    // kernels (p = 1, 2).  From p = 5 on the flux as one is the nearer one (P's error
+    // 2.37e-15 and 2.52e-15 at p = 5).
+    constexpr bool SPLIT = P < 5;
     const double *Ue = Ut + lt_base<P, double, D>(L);
-    const double ndd = A.nvec[4 * D], nuJ = A.nu * A.Jinv[4 * D];
+    const double ndd = A.nvec[4 * D];
     const double bl = sop[OL::bl], br = sop[OL::br];
-    double FIm[NA], FIp[NA], up[NA], X[NA][M];
+    double FIm[NA], FIp[NA], up[NA], X[NA][M], vm, vp;
     const double (&nm)[NA] = nb.nm;
     {
+        const double nuF = signed_nu(A.nu, ndd) * A.Jinv[4 * D];   // along the unit normal
         double um[NA], fm[3], fp[3];
 #pragma unroll
         for (int v = 0; v < NA; ++v) {
@@ -371,16 +385,18 @@ __device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const do
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             // the plus sides' slopes at their minus faces: the own one, the plus neighbour's
-            fm[c] = -nuJ * fma(br, up[1 + c], fma(bl, nm[1 + c], dot<M>(sop + OL::am, X[1 + c])));
-            fp[c] = -nuJ * fma(br, nb.pp[c], fma(bl, up[1 + c], nb.sp[c]));
+            fm[c] = -nuF * fma(br, up[1 + c], fma(bl, nm[1 + c], dot<M>(sop + OL::am, X[1 + c])));
+            fp[c] = -nuF * fma(br, nb.pp[c], fma(bl, up[1 + c], nb.sp[c]));
         }
-        acm_face<D>(nm, um, fm, A, FIm);
-        acm_face<D>(up, nb.np, fp, A, FIp);
+        acm_face<D, SPLIT>(nm, um, fm, A, FIm, vm);
+        acm_face<D, SPLIT>(up, nb.np, fp, A, FIp, vp);
+        if constexpr (SPLIT) pin(vm), pin(vp);
 #pragma unroll
         for (int v = 0; v < NA; ++v) pin(FIm[v]), pin(FIp[v]), pin(up[v]);
     }
     // the transformed fluxes of the velocities at the points, row by row with
     // the corrected derivative they contain
+    const double nuJ = A.nu * A.Jinv[4 * D];
     double F[3][M];
 #pragma unroll
     for (int r = 0; r < M; ++r) {
@@ -408,7 +424,10 @@ __device__ __forceinline__ void acm_line(const double *__restrict__ Ut, const do
         double Dr[M];
 #pragma unroll
         for (int l = 0; l < M; ++l) Dr[l] = sop[OL::Dt + r * M + l];
-        div[0][r] = fma(glr, FIm[0], fma(grr, FIp[0], zn * dot<M>(Dr, X[1 + D])));
+        if constexpr (SPLIT)
+            div[0][r] = fma(zn, fma(glr, vm, fma(grr, vp, dot<M>(Dr, X[1 + D]))), fma(glr, FIm[0], grr * FIp[0]));
+        else
+            div[0][r] = fma(glr, FIm[0], fma(grr, FIp[0], zn * dot<M>(Dr, X[1 + D])));
 #pragma unroll
         for (int c = 0; c < 3; ++c) div[1 + c][r] = fma(glr, FIm[1 + c], fma(grr, FIp[1 + c], dot<M>(Dr, F[c])));
 #pragma unroll

@@ -19,8 +19,8 @@ __device__ __forceinline__ void pin(T &x)
     __asm__ volatile("" : "+v"(x));
 }
 
-// nu with the sign of n (its unit normal's only entry, 1 or -1) on a face of a
-// diagonal Jacobian: the viscous part of the common flux for traces that are S_id
+// nu with the sign of n (a value with that of the unit normal's only entry, 1 or -1,
+// on a face of a diagonal Jacobian): the viscous part of the common flux for traces that are S_id
 // (trace_value).  On the bits, so that the sign of a kernel argument stays in the
 // scalar unit (held as three more arguments, or multiplied, it cost p = 6 in
 // double, which is at its register limit, 1.7 % of its residual).
