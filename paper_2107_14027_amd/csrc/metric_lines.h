@@ -470,9 +470,11 @@ __device__ __forceinline__ void metric_residual(const T *__restrict__ U, T *__re
             if constexpr (J == 2) o *= -(Geo::constant ? geo.inv_det(T(0)) : W[inner.at(r)]);
             q[inner.at(r)] = o;
         };
-        // the component is selected, not branched on: of three branches that
-        // differ in their registers alone the compiler (ROCm 7.2) merged the last
-        // stores and left the common factor unset for some lanes (p = 1)
+        // the component is selected, not branched on: with a branch for each of the
+        // three the compiler (ROCm 7.2) merges their stores and forms the third's
+        // address under the exec mask of the lanes that take the first, so that
+        // k = 2 stores to an unset address (seen in the assembly; wrong residuals at
+        // every order)
 #pragma unroll
         for (int r = 0; r < M; ++r) {
             const T a = part[1][r], b = part[2][r], c = part[3][r];
