@@ -1300,13 +1300,13 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 // ---------------------------------------------------------------------------
 // k_lines: stages 2-6 as line tasks (diagonal Jacobian).
 //
-// A workgroup takes LE consecutive elements: it copies their contiguous state
-// block into LDS (16-byte vectors where the element size allows), then runs
-// three groups of LW waves, one group per direction d.  A lane owns one line
-// of direction d of one element (face point L = a + m b of the faces 2d and
-// 2d+1).  It reads the m values of the seven variables the direction needs
-// (P, u, v, w and S_0d, S_1d, S_2d: with a diagonal Jacobian the transformed
-// flux along d involves no other), projects them to both ends of the line (the
+// A workgroup takes a brick of at most LE elements (Bricks): it loads their blocks
+// straight into LDS (slot_load), and three groups of LW waves work on them, one
+// group per direction d.  A lane owns one line of direction d of one element (face
+// point L = a + m b of the faces 2d and 2d+1).  It reads the m values of the seven
+// variables the direction needs (P, u, v, w and S_0d, S_1d, S_2d: with a diagonal
+// Jacobian the transformed flux along d involves no other), projects them to both
+// ends of the line (the
 // element's own traces, with k_trace's fma chain, so both sides of a face see
 // the same bits), reads the neighbours' traces, forms the two common fluxes,
 // the transformed flux at the m points and the six partially corrected
@@ -1449,11 +1449,12 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 #ifndef FR_LA6_F
 #define FR_LA6_F 2
 #endif
-// Waves per SIMD the register allocation of the line-form residual kernels aims
-// for (at least): 3 at p = 6 in double precision (168 VGPRs with a few values
-// spilled, against 171 VGPRs and two waves without the hint: 1.63 against
-// 2.13 ms per halo residual on 40^3 hexes); the stage-epilogue kernels take no
-// hint (three waves spill there and measured 15-58% slower in double precision).
+// Waves per SIMD the register allocation of the line-form kernels aims for (at
+// least), FR_LV for the residual and FR_LSV with the stage epilogue: 3 at p = 6 in
+// double (168 VGPRs, against two waves without the hint: 1.24 against 1.51 ms per
+// residual on 40^3 hexes, 7.9 against 11.1 ms per RK4 step); at p = 5 in double it is
+// even (1.06 and 1.07 ms on 43^3, 7.14 and 7.08).  All others reach their waves
+// without one.
 #ifndef FR_LV_DEFAULT
 #define FR_LV_DEFAULT 1
 #endif
@@ -1532,14 +1533,16 @@ __global__ void __launch_bounds__((Shape<P, T>::NT))
 // Largest lattice (elements) on which fr_rk_step and fr_dual_step apply the RK
 // stage update in the point form's kernel when the plan's residual is the halo
 // form by the automatic choice; larger ones take the halo form's epilogue.  RK4
-// steps, point against halo form: p = 4 in double 47 and 51 us on 4^3 hexes, 83
-// and 92 on 10^3, 137 and 126 on 12^3, 11.0 and 7.0 ms on 51^3 (few workgroups
-// leave the point form's trace pass cheap); p = 5 in single precision is within
-// 5% on a dozen elements (46 and 44 us) and 168 against 107 us on 10^3.
+// steps, point against halo form: p = 4 in double 57 and 60 us on 7^3 hexes, 62 and
+// 64 on 8^3, 73 and 78 on 9^3, 98 and 83 on 10^3, 130 and 104 on 12^3, 11.0 and 7.0 ms
+// on 51^3 (few workgroups leave the point form's trace pass cheap).  Below 7^3 (49 and
+// 45 us on 4^3), and for p = 5 in single precision on a dozen elements (48 and 45), the
+// halo form is up to 8 % ahead by now; the choice that FR_INFO_STAGE_PATH has reported
+// there is kept.
 template <int P, typename T>
 constexpr int stage_point_most()
 {
-    constexpr int d[PMAX + 1] = {0, 0, 0, 0, 1024, 0, 0}, f[PMAX + 1] = {0, 0, 0, 0, 0, 16, 0};
+    constexpr int d[PMAX + 1] = {0, 0, 0, 0, 800, 0, 0}, f[PMAX + 1] = {0, 0, 0, 0, 0, 16, 0};
     return sizeof(T) == 8 ? d[P] : f[P];
 }
 
@@ -2232,10 +2235,10 @@ __global__ void __launch_bounds__(FR_TLNT)
 
 // The whole residual in one kernel for a general constant Jacobian
 // (metric_lines.h): no traces in memory and one pass over the state instead of
-// two.  Bound by LDS (a line reads all thirteen variables).  p = 1..6 with some
-// 4 million points in FP64: 0.63 0.68 0.31 0.50 0.52 0.57 ms, the point form 1.07
-// 0.93 0.49 0.62 0.62 0.69; FP32 0.40 0.43 0.16 0.27 0.30 0.34, 0.66 0.53 0.24
-// 0.37 0.42 0.51.
+// two.  Bound by LDS (a line reads all thirteen variables).  p = 1..6 on 80^3 53^3
+// 40^3 32^3 27^3 23^3 hexes (4 million points) in FP64: 0.33 0.31 0.30 0.33 0.36 0.38
+// ms, the point form 0.59 0.47 0.49 0.43 0.46 0.49; FP32 0.19 0.19 0.14 0.16 0.19
+// 0.20, 0.37 0.27 0.23 0.27 0.31 0.35.
 template <int P, typename T>
 __global__ void __launch_bounds__(MetricShape<P>::NT)
     k_metric(const T *__restrict__ U, T *__restrict__ R, const T *__restrict__ ops, Consts<T> c, int nx, int ny,
@@ -2246,11 +2249,11 @@ __global__ void __launch_bounds__(MetricShape<P>::NT)
                           [&](int d, int, int, int) { return AffineGeo<T>(c, d); });
 }
 
-// FR_FORM_AUTO's smallest lattice of a general Jacobian on k_metric: from 4^3 the
-// one launch is ahead (p = 1..4 FP64 9 to 15 us, the two of the point form 18 to
-// 21); from p = 5 on it is even with them up to 8^3 (p = 6 FP64 27.5 and 26.5 us)
-// and ahead from 12^3 (68 and 82).  (FR_OPT_BLOCK is a setting of the point form's
-// kernel, which runs where it is set.)
+// Whether the residual runs k_metric: a general Jacobian under FR_FORM_AUTO, from
+// the lattice size on from which the one launch is ahead, 4^3 (p = 1..4 FP64 8 to 11
+// us, the two of the point form 17 to 21), from p = 5 on 10^3 (12^3: p = 5 FP64 38 and
+// 50 us, p = 6 56 and 79; on 8^3 it was even with the point form's 20 and 25).
+// FR_OPT_BLOCK is a setting of the point form's kernel, which runs where it is set.
 bool metric_takes(const fr_plan *pl)
 {
     return pl->variant == FR_FUSED && !pl->c64.diag && pl->form == FR_FORM_AUTO && !pl->block &&
