@@ -207,9 +207,13 @@ struct LinesTile {
     // banks (47 % of the halo form's LDS cycles were conflicts, 58 % of the general
     // Jacobian's); in the upper half of z the 16-byte chunks are therefore exchanged
     // two bits of (x, y) at a time, after which any 16 lines of one direction use
-    // different banks.  Odd m and m = 2, 6 spread by themselves.  General Jacobian
-    // on 40^3 elements 351 -> 314 us, linear hexes on 64^3 1.75 -> 1.63 ms, an RK4
-    // step on 64^3 5.32 -> 5.27 ms, its residual alone (memory-bound) even.
+    // different banks.  General Jacobian on 40^3 elements 351 -> 314 us (299 since),
+    // linear hexes on 64^3 1.75 -> 1.63 ms (1.42 since), an RK4 step on 64^3 5.32 -> 5.27
+    // ms (5.33), its residual alone (memory-bound) even.  The other shapes keep their
+    // order: within an element their lines spread, but where a slot is a multiple of
+    // the banks (p = 2 in double, p = 3 in single precision) a brick's elements meet in
+    // the same ones (5.1 and 4.0 conflict cycles an LDS instruction, 1.8 with the
+    // exchange).
     static constexpr bool SWZ = P == 3 && sizeof(T) == 8 && NVAR == NV;
     __device__ __forceinline__ static int place(int v) { return SWZ ? v ^ (v & 32 ? 6 : 0) : v; }
     __device__ __forceinline__ static int chunk(int c) { return SWZ ? c ^ (c & 16 ? 3 : 0) : c; }

@@ -259,8 +259,7 @@ int pseudo_iterate(fr_plan *pl, double *U, const double *B, double a, const doub
 int stage_blocks(int64_t n);
 // stage `stage` (0..3) of the separate path; single precision keeps the
 // accumulator in acc and the stage state in stT (velocities also in st64);
-// double precision keeps the stage states in place of the residuals (bufs of
-// RkStates)
+// double precision keeps the stage states in place of the residuals (RkBufs)
 int launch_stage32(fr_plan *pl, int stage, double *U, double *acc, double *st64, float *stT,
                    const float *k, const double *B, const double *D, double a, double b,
                    double cnext, double *partial, hipStream_t s);

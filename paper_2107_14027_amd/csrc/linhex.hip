@@ -312,8 +312,9 @@ __device__ __forceinline__ dev::TrilinearGeo line_metric(const double *__restric
 // start on 16-byte boundaries.  Floor 26 values per point and 24 per element
 // (0.71 ms at the rate of a copy for p = 4 on 51^3 hexes); what bounds it is the
 // FP64 and LDS work of a line, which reads all thirteen variables in every
-// direction.  p = 1..6 at the size of 51^3 p = 4: 2.0 1.9 1.6 1.8 1.8 2.3 ms, the
-// three kernels above 5.6 4.5 4.5 3.8 4.1 6.0; on 8^3 hexes 10 to 29 us, 30 to 55.
+// direction.  p = 1..6 on 128^3 85^3 64^3 51^3 43^3 36^3 hexes: 1.9 1.7 1.4 1.5 1.6
+// 1.6 ms, the three kernels above 5.5 4.5 4.5 3.8 4.2 4.4; on 8^3 hexes 8 to 27
+// us, 30 to 55.
 template <int P>
 __global__ void __launch_bounds__(dev::MetricShape<P>::NT) __attribute__((amdgpu_waves_per_eu(3, 8)))
     k_lh_lines(const double *__restrict__ corners, const double *__restrict__ U, double *__restrict__ R,

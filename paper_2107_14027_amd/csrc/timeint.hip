@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(TB) k_stage64(double *__restrict__ U, double *
 
 // One stage of the RK3(2)4[2R+]C pair (Kennedy, Carpenter and Lewis: four
 // stages, third order, embedded second order, two registers) with one
-// pseudo-step h per value, on dU/dtau = k* (k* as in k_stage).  With
+// pseudo-step h per value, on dU/dtau = k* (pseudo_rate).  With
 // hk = h k*:
 //   stages 0..2:  next = U + acc + anext hk;  acc += b hk;  err += bd hk
 //                 (acc, err start from zero on stage 0)
