@@ -38,12 +38,13 @@ def short(name):
         kern, p, t, extra = m.groups()
         # k_fused<P, T, DIAG, STG[, MF]>: STG selects the stage epilogue;
         # k_lines<P, T, HALO, STG>: HALO forms the neighbour traces from their
-        # states, STG != 0 applies an RK stage update
+        # states, STG & 3 applies an RK stage update (2: the last of a step)
         args = [a.strip() for a in extra.split(",") if a.strip()]
         if kern == "k_fused" and len(args) >= 2 and args[1] == "true":
             kern = "k_fused_stage"
         if kern == "k_lines" and args and args[0] == "true":
-            kern = "k_lines_halo" + ("_stage" if args[1:] and args[1] not in ("0", "false") else "")
+            stage = int(args[1]) & 3 if args[1:] and args[1].isdigit() else 0
+            kern = "k_lines_halo" + ("", "_stage", "_last")[stage]
         return "%s<%s,%s>" % (kern, p, t)
     m = re.search(r"(k_\w+)<([^>]*)>", name)
     if m:
@@ -112,7 +113,7 @@ def traffic(args):
     fs, fcal, fk, fn = res["FETCH_SIZE"]
     ws, wcal, wk, wn = res["WRITE_SIZE"]
     for k in sorted(set(fk) & set(wk)):
-        m = re.match(r"(k_fused|k_trace|k_lines|k_lines_halo|k_lines_halo_stage|k_trace_lines|k_fused_stage)<(\d+),(\w+)>", k)
+        m = re.match(r"(k_fused|k_trace|k_lines|k_lines_halo|k_lines_halo_stage|k_lines_halo_last|k_trace_lines|k_fused_stage)<(\d+),(\w+)>", k)
         if not m:
             continue
         tag = "%s_p%s_%s" % (m.group(1), m.group(2), "f64" if m.group(3) == "double" else "f32")
@@ -171,7 +172,7 @@ def counters(args):
            "| kernel | " + " | ".join(c[1] for c in cols) + " | bank conflict | ACTIVE_INST_VALU / BUSY_CYCLES | WAIT_INST_LDS / WAVE_CYCLES |",
            "|---|" + "---:|" * (len(cols) + 3)]
     for k in sorted(agg):
-        m = re.match(r"k_\w+<(\d+),", k)
+        m = re.match(r"k_(?!transfer)\w+<(\d+)[,>]", k)
         if not m or int(m.group(1)) not in pts:
             continue
         a = agg[k]
