@@ -22,7 +22,6 @@ struct Consts {
     T nmag[3];     // |n_d|
     T nhat[3][3];  // n_d / |n_d|
     T inv_det;     // 1 / det(J)
-    T jinv[3][3];  // J^{-1}: row d is n_d / det(J), rounded once
     T zeta, nu, invT;
     int diag;      // 1 when J is diagonal: n_hat_d = e_d exactly, or -e_d where J_dd < 0
 };

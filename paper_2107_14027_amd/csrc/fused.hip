@@ -2241,8 +2241,8 @@ __global__ void __launch_bounds__(FR_TLNT)
 // 0.20, 0.37 0.27 0.23 0.27 0.31 0.35.
 template <int P, typename T>
 __global__ void __launch_bounds__(MetricShape<P>::NT)
-    k_metric(const T *__restrict__ U, T *__restrict__ R, const T *__restrict__ ops, Consts<T> c, int nx, int ny,
-             int nz, Bricks g)
+    k_metric(const T *__restrict__ U, T *__restrict__ R, const T *__restrict__ ops, MetricConsts<T> c, int nx,
+             int ny, int nz, Bricks g)
 {
     __shared__ __align__(16) T smem[MetricLds<P, T, AffineGeo<T>>::size];
     metric_residual<P, T>(U, R, ops, c.zeta, c.nu, c.invT, nx, ny, nz, g, smem,
@@ -2326,7 +2326,7 @@ int fused_impl(fr_plan *pl, const T *U, T *R, const StageSpec *sp, int *nparts, 
             const Bricks &g = pl->metric_bricks[sizeof(T) == 8 ? FR_F64 : FR_F32];
             ProfScope ps(prof ? pl : nullptr, FR_K_FUSED, s);
             hipLaunchKernelGGL((k_metric<P, T>), dim3((g.nb + 7) / 8 * 8), dim3(MetricShape<P>::NT), 0, s, U, R,
-                               ops, c, pl->nx, pl->ny, pl->nz, g);
+                               ops, MetricConsts<T>(c, pl->Jinv), pl->nx, pl->ny, pl->nz, g);
             return check_hip(hipGetLastError(), "k_metric launch");
         }
     // persistent grid: every workgroup that fits on the device at once

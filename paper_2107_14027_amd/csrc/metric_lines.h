@@ -45,12 +45,25 @@ template <typename T> __device__ __forceinline__ OpPtr<T> op_row(OpPtr<T> p)
     return p;
 }
 
+// What k_metric takes beside the plan's constants.  In Consts itself the other kernels
+// paid for it: with J^{-1} among its arguments the halo form's residual took 43.3 us
+// in place of 40.7 at p = 2 on 25 x 24 x 43 hexes and 27.5 in place of 24.7 at p = 3
+// in single precision on 28 x 30 x 19 (lattices that fit the last-level cache).
+template <typename T>
+struct MetricConsts : Consts<T> {
+    T jinv[3][3];  // J^{-1}: row d is n_d / det(J), rounded once
+    MetricConsts(const Consts<T> &c, const double *Jinv) : Consts<T>(c)
+    {
+        for (int k = 0; k < 9; ++k) jinv[k / 3][k % 3] = (T)Jinv[k];
+    }
+};
+
 // Constant S_d, S_d / det J, |S_d| and 1 / det J of direction d.
 template <typename T>
 struct AffineGeo {
     static constexpr bool constant = true;
     T s[3], ji[3], nh[3], mag, idet;
-    __device__ __forceinline__ AffineGeo(const Consts<T> &c, int d)
+    __device__ __forceinline__ AffineGeo(const MetricConsts<T> &c, int d)
         : mag(d == 0 ? c.nmag[0] : (d == 1 ? c.nmag[1] : c.nmag[2])), idet(c.inv_det)
     {
 #pragma unroll

@@ -147,7 +147,6 @@ static void fill_consts(const fr_plan *pl, Consts<T> &c)
         c.nmag[d] = (T)mag;
         for (int j = 0; j < 3; ++j) {
             c.nvec[d][j] = (T)nv[j];
-            c.jinv[d][j] = (T)pl->Jinv[3 * d + j];
             c.nhat[d][j] = (T)(nv[j] / mag);
         }
     }
