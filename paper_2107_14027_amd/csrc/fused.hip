@@ -500,17 +500,20 @@ enum { STG_PLAIN = 0, STG_BDF = 1, STG_BDF_FIXED = 2 };   // the sources: none, 
 
 // Values per thread whose global operands the point form's stage epilogue requests
 // at once, per order, precision and use (a larger chunk overlaps more loads, until
-// its registers cost a wave of occupancy).  Measured on RK4 and dual steps on 4^3,
-// 12^3 and 24^3 hexes with a general Jacobian and 4^3, 16^3 with a diagonal one,
-// against one loop that decided stage and sources per value: RK4 steps 0.97 (p = 3
-// in single precision on 4^3) to 1.32 times as fast (p = 1 in double on 16^3), dual
-// steps 0.99 to 1.42.
+// its registers cost a wave of occupancy, which all uses of a kernel then pay: p = 1
+// in single precision with 13 and 8 values an RK4 step of a general Jacobian on 20^3
+// and 60^3 hexes took 0.089 and 1.25 ms, a dual pseudo-step on 60^3 1.64; with these
+// 0.096, 0.95 and 1.16).  Measured on RK4 and dual steps on 4^3 to 24^3 hexes (p = 1
+// in single precision to 60^3), general Jacobians and diagonal ones, against one loop
+// that decided stage and sources per value: RK4 steps 0.97 (p = 3 in single precision
+// on 4^3) to 1.32 times as fast (p = 1 in double on 16^3), dual steps 0.98 to 1.42.
 template <int P, typename T, bool DIAG, bool LAST, int SRC>
 constexpr int stage_chunk()
 {
-    constexpr int d[PMAX + 1] = {0, 7, 8, 7, 5, LAST ? 3 : 6, 6};
-    constexpr int plain[PMAX + 1] = {0, 13, LAST ? 11 : 6, DIAG ? 4 : 5, 5, LAST ? 8 : 4, 6};
-    constexpr int bdf[PMAX + 1] = {0, 8, 4, DIAG ? 4 : 5, 3, 4, 6};
+    constexpr int d[PMAX + 1] = {0, 7, 8, 7, 5, DIAG ? 6 : (LAST ? 4 : 7), LAST ? 7 : 6};
+    constexpr int plain[PMAX + 1] = {0, DIAG ? (LAST ? 10 : 6) : (LAST ? 7 : 8), LAST ? 11 : 6, DIAG ? 4 : 5, 5,
+                                     LAST ? 8 : 4, 6};
+    constexpr int bdf[PMAX + 1] = {0, 4, 4, DIAG ? 4 : 5, 3, 4, 6};
     return sizeof(T) == 8 ? d[P] : (SRC == STG_PLAIN ? plain[P] : bdf[P]);
 }
 
